@@ -127,7 +127,8 @@ def kernel_src_hash(read=None):
     `read(name)` returns a file's text (default: the working tree)."""
     read = read or (lambda f: open(os.path.join(ROOT, "paper_2606_27866_amd", "csrc", f)).read())
     h = hashlib.sha256()
-    for f in ("gemm_bf16_big.hip", "gemm_decode.hip", "gemv_decode.hip", "common.h", "kernels.h", "mfma_tile.h"):
+    for f in ("gemm_bf16_big.hip", "gemm_decode.hip", "gemv_decode.hip", "common.h", "kernels.h", "mfma_tile.h",
+              "mfma_pingpong.h"):
         for line in read(f).splitlines():
             code = line.split("//", 1)[0].rstrip()
             if code:

@@ -606,7 +606,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                     : decode     ? launch_gemm1_decode(p1, (int)n1, st)
                     : train == 1 ? launch_gemm1_big_train(p1, (int)n1, st)
                     : train == 2 ? launch_gemm1_big_train_rm(p1, (int)n1, st)
-                                 : launch_gemm1_big(p1, (int)n1, st, !sh, !use_side);
+                                 : launch_gemm1_big(p1, (int)n1, st, !use_side);
             }
             if (e != hipSuccess) return hip_fail(e, "gate/up GEMM launch");
             // the masked layer's down GEMM reduces over the kept channels only
@@ -621,7 +621,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                 KernelTimer kt(k2, st);
                 e = wide     ? launch_gemm2_decode_wide(p2, (int)n2, st)
                     : decode ? launch_gemm2_decode(p2, (int)n2, st)
-                             : launch_gemm2_big(p2, (int)n2, st, !sh);
+                             : launch_gemm2_big(p2, (int)n2, st);
             }
             if (e != hipSuccess) return hip_fail(e, "down GEMM launch");
         } else {
