@@ -10,20 +10,21 @@
 // so the weight gradients are never written: each wgrad tile reduces its
 // 256 x 256 block of (theta * g)^2 to one partial sum per channel.
 //
-// All are "NT" GEMMs: A rows and B rows are contiguous in K, staged by the
-// same LDS pipeline as the forward's big tiles (mfma_tile.h: 256 x 256 x 64
-// tiles, 8 waves as 2 x 4, direct-to-LDS DMA, three A and two B stages,
-// fragments one step ahead).  In the wgrad the MFMA takes the A fragment first, so a lane's
-// accumulator holds one B row (a channel) and runs of 4 consecutive A rows,
-// and the weight reads of its epilogue are 8-byte accesses.
+// All are "NT" GEMMs: A rows and B rows are contiguous in K; the K loop is the
+// forward's ping-pong loop over 256 x 256 tiles (mfma_pingpong.h).  In the
+// wgrad the MFMA takes the A fragment first, so a lane's accumulator holds one
+// B row (a channel) and runs of 4 consecutive A rows, and the weight reads of
+// its epilogue are 8-byte accesses.
+// On the Qwen1.5-MoE shape with 4096 tokens the loop took, against the one
+// before it (both waves of a SIMD on the same step, 32x32x16 MFMAs): wgrad
+// 568 -> 560,
+// saliency dgrad 238 -> 220, training dgrad 358 -> 318, dx 349 -> 320 us.
 //   dgrad: A = dO [A][d] (a segment's rows), B = W_down^T [E][I][d] (a
 //          transposed copy of the down weights), K = d.
 //   wgrad: A = x^T or dO^T [d][ldt], B = dG^T, dU^T or h^T [I][ldt], with a
 //          segment's rows as K (columns prow0 .. prow0 + rows of the
 //          transposed copies, zero-padded to a multiple of 8).
-#include <type_traits>
-
-#include "mfma_tile.h"
+#include "mfma_pingpong.h"
 #include "saliency.h"
 #include "train.h"
 
@@ -31,166 +32,32 @@ namespace flexmoe {
 
 namespace {
 using namespace mfma;
-constexpr int BM = 256, BN = 256;
-constexpr int NWAVE = 8, THREADS = 64 * NWAVE;
-constexpr int WAVES_PER_SIMD = NWAVE / 4;
-constexpr int WM = 2, WN = NWAVE / WM;      // wave grid
-constexpr int NF = BN / (WN * 32);          // 32-row B fragments per wave
-constexpr int WCOL = BN / WN;               // B rows per wave
-constexpr int NSTEP = BK / 16;
-static_assert(NSTEP == 4, "the K-loop schedule is laid out for four steps per K tile");
-constexpr int RPI = 64 / CHUNKS;            // LDS rows filled per DMA instruction
-constexpr int ROWS_PER_WAVE = BM / NWAVE;   // A rows (and B rows) each wave loads
-constexpr int NI = ROWS_PER_WAVE / RPI;     // DMA instructions per wave per operand
-constexpr int STAGE_A = BM * ROWB;
-constexpr int STAGE_B = BN * ROWB;
-constexpr int SMEM3 = 3 * STAGE_A + 2 * STAGE_B;  // the K loop's LDS with three A stages
-static_assert(SMEM3 <= 160 * 1024, "three A stages and two B stages fit one compute unit");
+constexpr int BM = PP_BM, BN = PP_BN, THREADS = PP_THREADS;
 constexpr int XCD_GROUP = 8;
 static_assert(BM == kSalTile && BN == kSalTile, "host tile counts use kSalTile");
 
-// The operands of one tile: per-lane byte offsets of the A and B rows this
-// lane loads (kOOB for rows outside the operand), the chunk column of each,
-// and the reduction length.
-struct NTOperands {
-    __amdgpu_buffer_rsrc_t ra, rb;
-    uint32_t aoff[NI], boff[NI];
-    int acol[NI];
-    int K;
-};
-
-// DMA instruction i of a wave fills LDS rows wave*ROWS_PER_WAVE + i*RPI ..
-// +RPI; lane -> row lane/CHUNKS, LDS chunk lane%CHUNKS, which holds global
-// chunk swz(row, lane%CHUNKS).  Rows at or past `valid` (counted from the
-// operand's base) read zeros.
-__device__ __forceinline__ void nt_rows(int wave, int lane, int row_base, int valid, int ld, uint32_t* off,
-                                        int* acol) {
+// Requested rows of an operand with rows of `ld` elements: A rows of the tile
+// whose first row is row_base (mf: its fragment count), B rows from row_base.
+// Rows at or past `valid` (counted from the operand's base) read zeros.
+__device__ __forceinline__ void nt_a_rows(int wave, int lane, int row_base, int valid, int ld, int mf,
+                                          PPOperands& op) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int r = wave * ROWS_PER_WAVE + i * RPI + lane / CHUNKS;
-        const int c = swz(r, lane % CHUNKS) * 8;
-        const int row = row_base + r;
-        acol[i] = c;
-        off[i] = row < valid ? (uint32_t)(((size_t)row * ld + c) * 2) : kOOB;
-    }
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < PP_ND; ++i) {
+            const int r = pp_lds_row(wave, lane, i), row = row_base + pp_a_row(h, r, mf);
+            op.col[i] = pp_col(wave, lane, i);
+            op.aoff[h][i] = r < 32 * mf && row < valid ? (uint32_t)(((size_t)row * ld + op.col[i]) * 2) : kOOB;
+        }
 }
-
-// Tail of a K loop that needs nothing after its last K tile: zero-page loads
-// keep the count of outstanding DMAs the schedule waits on.
-struct ZeroTail {
-    __amdgpu_buffer_rsrc_t r;
-    // one part (A or B) of a K-tile slot past the end
-    __device__ __forceinline__ void operator()(int, bool, unsigned char* dst) const {
+__device__ __forceinline__ void nt_b_rows(int wave, int lane, int row_base, int valid, int ld, PPOperands& op) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) load_lds16(r, kOOB, 0, dst + i * RPI * ROWB);
-    }
-};
-
-// The K loop of one tile whose waves multiply MFW 32-row A fragments each:
-// acc[i][j] = A rows wm*32*MFW + i*32 .. x B rows wn*WCOL + j*32 ...  The
-// schedule is the forward's: three A stages and two B stages (all 160 KB of
-// LDS; the A stages first, then the B stages), fragments read one step ahead,
-// A tile kt+2 requested beside the first MFMA step of tile kt, so each
-// barrier releases only the B tile's DMAs.  The last two DMA slots of each
-// part (K tiles nk and nk+1, past the end) go to tail(h, part_a, dst) for
-// h = 0, 1, which must issue exactly NI loads into this wave's rows `dst` of
-// A stage (nk + h) % 3 or of B stage (nk + h) % 2.
-// kSwap: the A fragment is the MFMA's first operand (lane -> B row, registers
-// -> runs of 4 A rows); otherwise the B fragment is (lane -> A row, registers
-// -> runs of 4 B rows).  zero = false continues accumulating into acc.
-template <int MFW, bool kSwap = true, typename Tail>
-__device__ __forceinline__ void nt_mainloop(unsigned char* smem, const NTOperands& op, int wave, int lane,
-                                            floatx16 (&acc)[MFW][NF], Tail&& tail, bool zero = true) {
-    constexpr int WR = 32 * MFW;
-    constexpr int NMF = MFW * NF;
-    constexpr int NRD = MFW + NF;
-    const int wm = wave / WN, wn = wave % WN;
-    if (zero) {
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int i = 0; i < MFW; ++i)
-#pragma unroll
-            for (int j = 0; j < NF; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    }
-
-    const int nk = ceil_div(op.K, BK);
-    bf16x8 a[2][MFW], b[2][NF];
-    auto read_frags = [&](int kt, int ks, int buf) {
-        const unsigned char* sa = smem + (kt % 3) * STAGE_A;
-        const unsigned char* sb = smem + 3 * STAGE_A + (kt % 2) * STAGE_B;
-        const int chunk = ks * 2 + (lane >> 5);
-#pragma unroll
-        for (int i = 0; i < MFW; ++i) a[buf][i] = lds_frag(sa, wm * WR + i * 32 + (lane & 31), chunk);
-#pragma unroll
-        for (int j = 0; j < NF; ++j) b[buf][j] = lds_frag(sb, wn * WCOL + j * 32 + (lane & 31), chunk);
-    };
-    auto mfma_step = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < MFW; ++i)
-#pragma unroll
-            for (int j = 0; j < NF; ++j)
-                acc[i][j] = kSwap ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[buf][i], b[buf][j], acc[i][j], 0, 0, 0)
-                                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[buf][j], a[buf][i], acc[i][j], 0, 0, 0);
-    };
-    // DMA of K tile kt's A part into A stage kt % 3, or its B part into
-    // B stage kt % 2 (masked past K)
-    auto issue_part = [&](int kt, bool part_a) {
-        unsigned char* dst = (part_a ? smem + (kt % 3) * STAGE_A : smem + 3 * STAGE_A + (kt % 2) * STAGE_B) +
-                             wave * ROWS_PER_WAVE * ROWB;
-        if (kt >= nk) {
-            tail(kt - nk, part_a, dst);
-            return;
+        for (int i = 0; i < PP_ND; ++i) {
+            const int row = row_base + h * PP_HALF_ROWS + pp_lds_row(wave, lane, i);
+            op.boff[h][i] = row < valid ? (uint32_t)(((size_t)row * ld + pp_col(wave, lane, i)) * 2) : kOOB;
         }
-        const int lim = op.K - kt * BK;
-        const uint32_t soff = (uint32_t)(kt * BK) * 2u;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const bool kin = op.acol[i] < lim;
-            if (part_a) load_lds16(op.ra, kin ? op.aoff[i] : kOOB, soff, dst + i * RPI * ROWB);
-            else load_lds16(op.rb, kin ? op.boff[i] : kOOB, soff, dst + i * RPI * ROWB);
-        }
-    };
-    issue_part(0, true);
-    issue_part(0, false);
-    issue_part(1, true);
-    issue_part(1, false);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * NI));  // tile 0 in
-    barrier_no_fence();
-    read_frags(0, 0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        read_frags(kt, 1, 1);
-        issue_part(kt + 2, true);  // into the A stage of tile kt-1, free since the last barrier
-        mfma_step(0);
-        sched_interleave<NMF, NI, NRD>();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int st = 1; st < NSTEP - 1; ++st) {
-            read_frags(kt, st + 1, (st + 1) & 1);
-            mfma_step(st & 1);
-            sched_interleave<NMF, 0, NRD>();
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(NI) & kWaitLgkm0);  // tile kt+1 in; own reads done
-        barrier_no_fence();
-        __builtin_amdgcn_sched_barrier(0);
-        issue_part(kt + 2, false);
-        read_frags(kt + 1, 0, 0);
-        mfma_step((NSTEP - 1) & 1);
-        sched_interleave<NMF, NI, NRD>();
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // no DMA may outlive the workgroup's LDS
-}
-
-// Runs `body` with the fragment count for a tile of `rows` A rows (the two
-// M-waves cover 64*MFW rows).
-template <typename F>
-__device__ __forceinline__ void by_rows(int rows, F&& body) {
-    if (rows > 3 * 64) body(std::integral_constant<int, 4>{});
-    else if (rows > 2 * 64) body(std::integral_constant<int, 3>{});
-    else if (rows > 64) body(std::integral_constant<int, 2>{});
-    else body(std::integral_constant<int, 1>{});
 }
 
 // Tile of this workgroup when groups of `group` consecutive tiles go to one
@@ -211,8 +78,8 @@ __device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w 
 
 // ---- wgrad + saliency: one tile = 256 hidden units x 256 channels of one
 // (matrix, expert) ----------------------------------------------------------
-__global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void sal_wgrad_kernel(SalWgradParams p) {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM3];
+__global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void sal_wgrad_kernel(SalWgradParams p) {
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[PP_SMEM];
     // all tiles of one (matrix, expert) on one XCD: they share its x^T (or
     // dO^T) rows and its dG^T (dU^T, h^T) rows
     const int L = xcd_tile(p.nI * p.nM);
@@ -223,89 +90,93 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void sal_wgrad_kernel(SalW
     rest /= p.nI;
     const int e = rest % p.E, mat = rest / p.E;
     const SegMeta sm = p.seg[p.hs + e];
-    const int MP = p.nM * WM;  // partial sums per channel
+    const int MP = p.nM * kSalWaveM;  // partial sums per channel
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave >> 2, wn = wave & 3;
     float* part_out = p.partial + ((size_t)mat * p.E + e) * p.I * MP;
 
     if (sm.rows == 0) {  // no token reached the expert: its gradient is zero
-        if (lane < 32)
-#pragma unroll
-            for (int j = 0; j < NF; ++j) {
-                const int c = ntile * BN + wn * WCOL + j * 32 + lane;
-                if (c < p.I) part_out[(size_t)c * MP + mtile * WM + wm] = 0.f;
-            }
+        if (lane < 32) {
+            const int c = ntile * BN + wn * 64 + lane;
+            if (c < p.I) part_out[(size_t)c * MP + mtile * kSalWaveM + wm] = 0.f;
+            if (c + 32 < p.I) part_out[(size_t)(c + 32) * MP + mtile * kSalWaveM + wm] = 0.f;
+        }
         return;
     }
 
     const bf16_t* A = p.a[mat] + sm.prow0;
     const bf16_t* B = p.b[mat] + sm.prow0;
-    NTOperands op;
+    const int mf = pp_mf(p.d - mtile * BM);
+    PPOperands op;
     op.K = sm.rows;
     op.ra = make_rsrc(A, (size_t)p.d * p.ldt - sm.prow0);
-    op.rb = make_rsrc(B, (size_t)p.I * p.ldt - sm.prow0);
-    int bcol[NI];
-    nt_rows(wave, lane, mtile * BM, p.d, p.ldt, op.aoff, op.acol);
-    nt_rows(wave, lane, ntile * BN, p.I, p.ldt, op.boff, bcol);
+    op.rb[0] = op.rb[1] = make_rsrc(B, (size_t)p.I * p.ldt - sm.prow0);
+    nt_a_rows(wave, lane, mtile * BM, p.d, p.ldt, mf, op);
+    nt_b_rows(wave, lane, ntile * BN, p.I, p.ldt, op);
 
     // theta = W[c][m] of the tile's 256 channels x 256 hidden units (gate, up
-    // or the transposed down weight), brought into the operand stages by the
-    // loop's last two DMA slots, while its last K tiles are multiplied.
-    // Slot h holds channels h*128 .. +128, one 512-byte row each: rows 0..63
-    // in A stage (nk + h) % 3, rows 64..127 in B stage (nk + h) % 2; 16-byte
-    // chunk pos of row r holds hidden units 8 * (pos ^ (r % 32)) ..
+    // or the transposed down weight), brought into the operand halves by the
+    // loop's last eight requests, while its last K tiles are multiplied.
+    // Half `half` of slot h holds channels (4h + half) * 32 .. +32, one
+    // 512-byte row each; 16-byte chunk pos of row r holds hidden units
+    // 8 * (pos ^ r) ..
     const bf16_t* W = p.w[mat] + (size_t)e * p.I * p.d;
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(W, (size_t)p.I * p.d);
-    auto theta_tail = [&](int h, bool part_a, unsigned char* dst) {
-        const int part = part_a ? 0 : 1;
+    auto theta_tail = [&](int half, int h, unsigned char* dst) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int tr = part * 64 + wave * 8 + 2 * i + (lane >> 5);  // theta row of the slot
-            const int c = ntile * BN + h * 128 + tr;
-            const int m = mtile * BM + ((lane & 31) ^ (tr & 31)) * 8;
+        for (int i = 0; i < PP_ND; ++i) {
+            const int tr = wave * 2 * PP_ND + 2 * i + (lane >> 5);  // theta row of the half
+            const int c = ntile * BN + (h * 4 + half) * 32 + tr;
+            const int m = mtile * BM + ((lane & 31) ^ tr) * 8;
             const uint32_t off = c < p.I && m < p.d ? (uint32_t)(((size_t)c * p.d + m) * 2) : kOOB;
-            load_lds16(rw, off, 0, dst + i * RPI * ROWB);
+            load_lds16(rw, off, 0, dst + i * PP_RPI * ROWB);
         }
     };
     const int nk = ceil_div(op.K, BK);
-    by_rows(p.d - mtile * BM, [&](auto tag) {
-        constexpr int MFW = decltype(tag)::value;
-        floatx16 acc[MFW][NF];
-        nt_mainloop<MFW, true>(smem, op, wave, lane, acc, theta_tail);
-        barrier_no_fence();  // every wave's theta DMAs have landed
-        // epilogue: lane -> channel c, register v -> hidden unit
-        // 8(v/4) + 4(lane/32) + v%4 of a fragment; (theta * dW)^2 summed
-        float part[NF];
+    auto theta_half = [&](int half, int h) { return smem + (((nk + h) & 1) * 4 + half) * PP_HALF; };
+    pp_by_rows(p.d - mtile * BM, [&](auto tag) {
+        constexpr int MF = decltype(tag)::value;
+        PPAcc<MF> acc;
+        pp_loop<MF, true>(smem, op, wave, lane, acc, theta_tail);
+        // the half the loop never refills; its last reads are done
+        theta_tail(1, 1, theta_half(1, 1) + wave * (PP_ND * PP_RPI) * ROWB);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        barrier_no_fence();  // every wave's theta requests have landed
+        // epilogue: lane -> channel, register v -> hidden unit
+        // 4(lane/16) + v of a fragment; (theta * dW)^2 summed
+        float part[2][2];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) {
-            part[j] = 0.f;
-            const int cl = wn * WCOL + j * 32 + (lane & 31);  // channel within the tile
-            const int h = cl >> 7, tr = cl & 127;
-            const unsigned char* trow = (tr < 64 ? smem + ((nk + h) % 3) * STAGE_A
-                                                 : smem + 3 * STAGE_A + ((nk + h) % 2) * STAGE_B) +
-                                        (tr & 63) * 512;
+        for (int bh = 0; bh < 2; ++bh)
 #pragma unroll
-            for (int i = 0; i < MFW; ++i)
+            for (int j = 0; j < 2; ++j) {
+                float s = 0.f;
+                const int cl = pp_frag_col(bh, wn, j) + (lane & 15);  // channel within the tile
+                const unsigned char* trow = theta_half((cl >> 5) & 3, cl >> 7) + (cl & 31) * 512;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int ml = wm * 32 * MFW + i * 32 + q * 8 + (lane >> 5) * 4;
-                    const uint2 th = *reinterpret_cast<const uint2*>(
-                        trow + (((ml >> 3) ^ (cl & 31)) << 4) + (ml & 7) * 2);
-                    const float t0 = lo_bf16(th.x) * acc[i][j][q * 4 + 0];
-                    const float t1 = hi_bf16(th.x) * acc[i][j][q * 4 + 1];
-                    const float t2 = lo_bf16(th.y) * acc[i][j][q * 4 + 2];
-                    const float t3 = hi_bf16(th.y) * acc[i][j][q * 4 + 3];
-                    part[j] += (t0 * t0 + t1 * t1) + (t2 * t2 + t3 * t3);
-                }
-        }
+                for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
-        for (int j = 0; j < NF; ++j) part[j] += __shfl_xor(part[j], 32, 64);
-        if (lane < 32)
-#pragma unroll
-            for (int j = 0; j < NF; ++j) {
-                const int c = ntile * BN + wn * WCOL + j * 32 + lane;
-                if (c < p.I) part_out[(size_t)c * MP + mtile * WM + wm] = part[j];
+                    for (int i = 0; i < MF; ++i) {
+                        const int ml = pp_frag_row<MF>(ah, wm, i) + (lane >> 4) * 4;
+                        const uint2 th = *reinterpret_cast<const uint2*>(
+                            trow + (((ml >> 3) ^ (cl & 31)) << 4) + (ml & 7) * 2);
+                        const floatx4 g = acc[ah][bh][j * MF + i];
+                        const float t0 = lo_bf16(th.x) * g[0];
+                        const float t1 = hi_bf16(th.x) * g[1];
+                        const float t2 = lo_bf16(th.y) * g[2];
+                        const float t3 = hi_bf16(th.y) * g[3];
+                        s += (t0 * t0 + t1 * t1) + (t2 * t2 + t3 * t3);
+                    }
+                s += __shfl_xor(s, 16, 64);
+                part[bh][j] = s + __shfl_xor(s, 32, 64);
             }
+        if (lane < 16)
+#pragma unroll
+            for (int bh = 0; bh < 2; ++bh)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int c = ntile * BN + pp_frag_col(bh, wn, j) + lane;
+                    if (c < p.I) part_out[(size_t)c * MP + mtile * kSalWaveM + wm] = part[bh][j];
+                }
     });
 }
 
@@ -355,13 +226,13 @@ __device__ __forceinline__ bool train_tile(const SegMeta* seg, int hs, int nseg,
 //     padding rows -- for the weight-gradient GEMMs.
 constexpr int DG_PITCH = BN / 2 + 8;                  // staged row (bf16): 272 bytes, 16-byte aligned
 constexpr int DG_STAGE = BM * DG_PITCH * 2;           // one staged array
-constexpr int DG_SMEM = (2 * DG_STAGE > SMEM3) ? 2 * DG_STAGE : SMEM3;
+constexpr int DG_SMEM = (2 * DG_STAGE > PP_SMEM) ? 2 * DG_STAGE : PP_SMEM;
 constexpr int DG_TPITCH = BM + 8;                     // transposed staging row (bf16): 4 rows = 16 banks
 static_assert(2 * (BN / 2) * DG_TPITCH * 2 <= DG_SMEM, "the transposed staging fits");
 static_assert(DG_SMEM <= 160 * 1024, "the dgrad LDS fits one compute unit");
 
 template <int kMode>
-__global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgradParams p) {
+__global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void dgrad_kernel(ActDgradParams p) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[DG_SMEM];
     SegMeta sm;
     int mtile, ntile;
@@ -371,17 +242,17 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
     const bool shared = sm.e < 0;
     const int C = shared ? p.Is : p.I;  // channels (row length of g, u, dG, dU)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave >> 2, wn = wave & 3;
 
-    NTOperands op;
+    const int mf = pp_mf(sm.rows - mtile * BM);
+    PPOperands op;
     op.K = p.d;
     const bf16_t* A = shared ? p.dYs : p.dO + (size_t)sm.row0 * p.d;
     const bf16_t* B = shared ? p.wsdt : p.wdt + (size_t)sm.e * p.I * p.d;
     op.ra = make_rsrc(A, (size_t)sm.rows * p.d);
-    op.rb = make_rsrc(B, (size_t)C * p.d);
-    int bcol[NI];
-    nt_rows(wave, lane, mtile * BM, sm.rows, p.d, op.aoff, op.acol);
-    nt_rows(wave, lane, ntile * BN, C, p.d, op.boff, bcol);
+    op.rb[0] = op.rb[1] = make_rsrc(B, (size_t)C * p.d);
+    nt_a_rows(wave, lane, mtile * BM, sm.rows, p.d, mf, op);
+    nt_b_rows(wave, lane, ntile * BN, C, p.d, op);
 
     const size_t rbase = shared ? 0 : (size_t)sm.row0;
     const bf16_t* G = shared ? p.Gs : p.G;
@@ -392,28 +263,31 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
     const int kk8 = min(packed_width(kk), C);    // dG/dU columns the dx GEMM reads
     bf16_t* stg = reinterpret_cast<bf16_t*>(smem);
     bf16_t* stu = stg + (kMode == 2 ? BM * DG_PITCH : (BN / 2) * DG_TPITCH);
-    by_rows(sm.rows - mtile * BM, [&](auto tag) {
-        constexpr int MFW = decltype(tag)::value;
-        floatx16 acc[MFW][NF];
-        nt_mainloop<MFW, false>(smem, op, wave, lane, acc, ZeroTail{op.ra});
-        // the stages are free once every wave is past its last fragment read
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    pp_by_rows(sm.rows - mtile * BM, [&](auto tag) {
+        constexpr int MF = decltype(tag)::value;
+        PPAcc<MF> acc;
+        pp_loop<MF, false>(smem, op, wave, lane, acc, PPZeroTail{});
+        // the operand halves are free once no wave has requests in flight
         barrier_no_fence();
-        // epilogue: lane -> row (lane%32 of a fragment), register v ->
-        // channel 8(v/4) + 4(lane/32) + v%4 of a 32-channel fragment
-        float msum[NF][16];
+        // epilogue: lane -> row (lane%16 of a fragment), register v ->
+        // channel 4(lane/16) + v of a 16-channel fragment
+        float msum[2][2][4];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) {
+        for (int bh = 0; bh < 2; ++bh) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) msum[j][v] = 0.f;
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int i = 0; i < MFW; ++i) {
-                const int row = wm * 32 * MFW + i * 32 + (lane & 31);  // row of the tile
-                const int grow = mtile * BM + row;                     // row of the segment
+                for (int v = 0; v < 4; ++v) msum[bh][j][v] = 0.f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int cl = wn * 32 + q * 8 + (lane >> 5) * 4;  // staged column of this half
-                    const int c0 = ntile * BN + wn * WCOL + j * 32 + q * 8 + (lane >> 5) * 4;
+            for (int ah = 0; ah < 2; ++ah)
+#pragma unroll
+            for (int i = 0; i < MF; ++i) {
+                const int row = pp_frag_row<MF>(ah, wm, i) + (lane & 15);  // row of the tile
+                const int grow = mtile * BM + row;                         // row of the segment
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int cl = pp_frag_col(0, wn, j) + (lane >> 4) * 4;  // staged column of this half
+                    const int c0 = ntile * BN + bh * PP_HALF_ROWS + cl;
                     uint32_t dg[2] = {0u, 0u}, du[2] = {0u, 0u};
                     if (grow < sm.rows && c0 < C) {
                         const size_t off = frag_blocked(rbase + grow, c0, C);
@@ -425,8 +299,8 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
                         for (int r = 0; r < 4; ++r) {
                             const float x = g[r];
                             const float sg = 1.0f / (1.0f + __builtin_amdgcn_exp2f(-x * 1.4426950408889634f));
-                            const float dh = acc[i][j][q * 4 + r];
-                            if constexpr (kMode == 2) msum[j][q * 4 + r] += dh * (x * sg) * u[r];
+                            const float dh = acc[ah][bh][j * MF + i][r];
+                            if constexpr (kMode == 2) msum[bh][j][r] += dh * (x * sg) * u[r];
                             const bool kept = c0 + r < kk;
                             const float vg = kept ? dh * u[r] * (sg * (1.0f + x * (1.0f - sg))) : 0.f;
                             const float vu = kept ? dh * (x * sg) : 0.f;
@@ -447,12 +321,12 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
                 }
             }
             __syncthreads();
-            // staged column cl of half j is channel ntile*BN + (cl/32)*WCOL + j*32 + cl%32
+            // staged column cl of half bh is channel ntile*BN + bh*128 + cl
             if constexpr (kMode == 2) {
                 for (int k = threadIdx.x; k < BM * (BN / 2 / 8); k += THREADS) {
                     const int row = k / (BN / 2 / 8), cl = (k % (BN / 2 / 8)) * 8;
                     const int grow = mtile * BM + row;
-                    const int c = ntile * BN + (cl / 32) * WCOL + j * 32 + cl % 32;
+                    const int c = ntile * BN + bh * PP_HALF_ROWS + cl;
                     if (grow >= sm.rows || c >= kk8) continue;
                     const size_t o = (rbase + grow) * (size_t)C + c;
                     *reinterpret_cast<u32x4*>(dG + o) = *reinterpret_cast<const u32x4*>(stg + row * DG_PITCH + cl);
@@ -464,7 +338,7 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
                 const size_t col = (size_t)sm.prow0 + mtile * BM;
                 for (int k = threadIdx.x; k < (BN / 2) * (BM / 8); k += THREADS) {
                     const int cl = k / (BM / 8), r0 = (k % (BM / 8)) * 8;
-                    const int c = ntile * BN + (cl / 32) * WCOL + j * 32 + cl % 32;
+                    const int c = ntile * BN + bh * PP_HALF_ROWS + cl;
                     if (r0 >= pvalid || c >= C) continue;
                     const size_t o = (size_t)c * p.ldt + col + r0;
                     *reinterpret_cast<u32x4*>(dG + o) = *reinterpret_cast<const u32x4*>(stg + cl * DG_TPITCH + r0);
@@ -474,35 +348,37 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void dgrad_kernel(ActDgrad
             __syncthreads();
         }
         if (kMode == 1 || shared) return;
-        // mask-gradient partial sums: over the 32 rows of the lane group
+        // mask-gradient partial sums: over the 16 rows of the lane group
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
+        for (int bh = 0; bh < 2; ++bh)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float t = msum[j][v];
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int o = 1; o < 32; o <<= 1) t += __shfl_xor(t, o, 64);
-                msum[j][v] = t;
-            }
-        if ((lane & 31) == 0) {
+                for (int v = 0; v < 4; ++v) {
+                    float t = msum[bh][j][v];
+#pragma unroll
+                    for (int o = 1; o < 16; o <<= 1) t += __shfl_xor(t, o, 64);
+                    msum[bh][j][v] = t;
+                }
+        if ((lane & 15) == 0) {
             float* out = p.dmp + ((size_t)(sm.rt0 + mtile) * kTrainWaveM + wm) * p.I;
 #pragma unroll
-            for (int j = 0; j < NF; ++j)
+            for (int bh = 0; bh < 2; ++bh)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int c = ntile * BN + wn * WCOL + j * 32 + q * 8 + (lane >> 5) * 4 + r;
-                        if (c < p.I) out[c] = msum[j][q * 4 + r];
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = ntile * BN + pp_frag_col(bh, wn, j) + (lane >> 4) * 4 + v;
+                        if (c < p.I) out[c] = msum[bh][j][v];
                     }
         }
     });
 }
 
 // dX = dG W_gate + dU W_up over the kept channels; tile = 256 rows x 256
-// hidden units, two K loops into one accumulator.
-__global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void act_dx_kernel(ActDxParams p) {
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM3];
+// hidden units, one K loop over both products.
+__global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void act_dx_kernel(ActDxParams p) {
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[PP_SMEM];
     SegMeta sm;
     int mtile, ntile;
     if (!train_tile(p.seg, p.hs, p.nseg, p.T, p.Is, p.nD, p.nD, xcd_tile(dgrad_group(p.nD)), sm, mtile, ntile))
@@ -510,53 +386,40 @@ __global__ __launch_bounds__(THREADS, WAVES_PER_SIMD) void act_dx_kernel(ActDxPa
     const bool shared = sm.e < 0;
     const int C = shared ? p.Is : p.I;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave >> 2, wn = wave & 3;
     const size_t rbase = shared ? 0 : (size_t)sm.row0;
 
-    NTOperands og, ou;
-    og.K = ou.K = sm.kk;
+    const int mf = pp_mf(sm.rows - mtile * BM);
+    PPOperands op;
+    op.K = sm.kk;
     const bf16_t* Ag = (shared ? p.dGs : p.dG) + rbase * C;
     const bf16_t* Au = (shared ? p.dUs : p.dU) + rbase * C;
     const bf16_t* Bg = shared ? p.wsgt : p.wgt + (size_t)sm.e * p.d * p.I;
     const bf16_t* Bu = shared ? p.wsut : p.wut + (size_t)sm.e * p.d * p.I;
-    og.ra = make_rsrc(Ag, (size_t)sm.rows * C);
-    ou.ra = make_rsrc(Au, (size_t)sm.rows * C);
-    og.rb = make_rsrc(Bg, (size_t)p.d * C);
-    ou.rb = make_rsrc(Bu, (size_t)p.d * C);
-    int bcol[NI];
-    nt_rows(wave, lane, mtile * BM, sm.rows, C, og.aoff, og.acol);
-    nt_rows(wave, lane, ntile * BN, p.d, C, og.boff, bcol);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        ou.aoff[i] = og.aoff[i];
-        ou.boff[i] = og.boff[i];
-        ou.acol[i] = og.acol[i];
-    }
+    const PPSecond pairs{Ag, Au, Bg, Bu, (size_t)sm.rows * C, (size_t)p.d * C};
+    nt_a_rows(wave, lane, mtile * BM, sm.rows, C, mf, op);
+    nt_b_rows(wave, lane, ntile * BN, p.d, C, op);
     float* out = (shared ? p.dXs : p.dXr) + rbase * p.d;
-    by_rows(sm.rows - mtile * BM, [&](auto tag) {
-        constexpr int MFW = decltype(tag)::value;
-        floatx16 acc[MFW][NF];
-        nt_mainloop<MFW, false>(smem, og, wave, lane, acc, ZeroTail{og.ra});
-        // every wave is past its last LDS read before the second loop refills the stages
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-        barrier_no_fence();
-        nt_mainloop<MFW, false>(smem, ou, wave, lane, acc, ZeroTail{ou.ra}, false);
+    pp_by_rows(sm.rows - mtile * BM, [&](auto tag) {
+        constexpr int MF = decltype(tag)::value;
+        PPAcc<MF> acc;
+        pp_loop<MF, false>(smem, op, wave, lane, acc, PPZeroTail{}, pairs);
         // epilogue: lane -> row, registers -> runs of 4 hidden units
 #pragma unroll
-        for (int i = 0; i < MFW; ++i) {
-            const int row = mtile * BM + wm * 32 * MFW + i * 32 + (lane & 31);
-            if (row >= sm.rows) continue;
+        for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
-            for (int j = 0; j < NF; ++j)
+            for (int i = 0; i < MF; ++i) {
+                const int row = mtile * BM + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
+                if (row >= sm.rows) continue;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n0 = ntile * BN + wn * WCOL + j * 32 + q * 8 + (lane >> 5) * 4;
-                    if (n0 >= p.d) continue;
-                    *reinterpret_cast<float4*>(out + (size_t)row * p.d + n0) =
-                        make_float4(acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
-                                    acc[i][j][q * 4 + 3]);
-                }
-        }
+                for (int bh = 0; bh < 2; ++bh)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int n0 = ntile * BN + pp_frag_col(bh, wn, j) + (lane >> 4) * 4;
+                        if (n0 >= p.d) continue;
+                        *reinterpret_cast<floatx4*>(out + (size_t)row * p.d + n0) = acc[ah][bh][j * MF + i];
+                    }
+            }
     });
 }
 

@@ -67,6 +67,14 @@ struct PPOperands {
     int K;
 };
 
+// Two pairs of operands with the same rows, offsets, extents (in elements) and
+// K: C = A B^T + A2 B2^T, the K tiles of the second pair after those of the
+// first (ra and rb of PPOperands are then unused).
+struct PPSecond {
+    const bf16_t *a, *a2, *b, *b2;
+    size_t aext, bext;
+};
+
 // LDS row (within a half) and K chunk column of DMA instruction i.
 __device__ __forceinline__ int pp_lds_row(int wave, int lane, int i) {
     return wave * (PP_ND * PP_RPI) + i * PP_RPI + lane / CHUNKS;
@@ -98,41 +106,52 @@ __device__ __forceinline__ int pp_frag_col(int h, int wn, int j) { return h * PP
 
 // Tail of a K loop that needs nothing after its last K tile: the requests past
 // the end read zeros.
-struct PPZeroTail {};
+struct PPZeroTail {
+    __device__ __forceinline__ void operator()(int, int, unsigned char*) const {}
+};
+
+// No second pair.
+struct PPNoSecond {};
 
 // Runs the K loop.  Requests for K tiles past the end (slot h = kt - nk is 0
 // or 1) go to tail(half, h, dst), half 0..3 = A0 A1 B0 B1, which must issue
 // exactly PP_ND loads into this wave's rows `dst` of that half; half 1 (A1)
-// of slot 1 is never requested.  On return no request is in flight and every
-// wave has finished its LDS reads (the last barrier is behind them).
-// zero = false continues accumulating into acc.
-template <int MF, bool kSwap, typename Tail>
+// of slot 1 is never requested.  On return this wave has no request in flight
+// and every wave has finished its LDS reads.
+template <int MF, bool kSwap, typename Tail, typename Second = PPNoSecond>
 __device__ __forceinline__ void pp_loop(unsigned char* smem, const PPOperands& op, int wave, int lane,
-                                        PPAcc<MF>& acc, Tail&& tail, bool zero = true) {
+                                        PPAcc<MF>& acc, Tail&& tail, Second sec = Second{}) {
+    constexpr bool kTail = !std::is_same<std::decay_t<Tail>, PPZeroTail>::value;
+    constexpr bool kSecond = std::is_same<Second, PPSecond>::value;
     const int wm = wave >> 2, wn = wave & 3;
-    const int nk = ceil_div(op.K, BK);
-    if (zero) {
+    const int nk1 = ceil_div(op.K, BK), nk = kSecond ? 2 * nk1 : nk1;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int f = 0; f < 2 * MF; ++f) acc[q >> 1][q & 1][f] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int f = 0; f < 2 * MF; ++f) acc[q >> 1][q & 1][f] = floatx4{0.f, 0.f, 0.f, 0.f};
     // half 0: A0, 1: A1, 2: B0, 3: B1
-    auto request = [&](int half, int kt) {
+    auto request = [&](int half, int kt, auto may_end) {
         unsigned char* dst = smem + ((kt & 1) * 4 + half) * PP_HALF + wave * (PP_ND * PP_RPI) * ROWB;
-        if constexpr (!std::is_same<std::decay_t<Tail>, PPZeroTail>::value)
+        if constexpr (kTail && decltype(may_end)::value)
             if (kt >= nk) {
                 tail(half, kt - nk, dst);
                 return;
             }
+        __amdgpu_buffer_rsrc_t r = half < 2 ? op.ra : op.rb[half & 1];
+        if constexpr (kSecond) {
+            const bool second = kt >= nk1;
+            r = half < 2 ? make_rsrc(second ? sec.a2 : sec.a, sec.aext) : make_rsrc(second ? sec.b2 : sec.b, sec.bext);
+            if (second) kt -= nk1;
+        }
         // past the end `lim` is not positive: every lane's offset is kOOB, with
-        // no branch in the loop
+        // no branch in the loop (branches around the requests cost 8 % of a
+        // dense product)
         const int lim = op.K - kt * BK;
         const uint32_t soff = (uint32_t)(kt * BK) * 2u;
 #pragma unroll
         for (int i = 0; i < PP_ND; ++i) {
             const uint32_t o = half < 2 ? op.aoff[half & 1][i] : op.boff[half & 1][i];
-            load_lds16(half < 2 ? op.ra : op.rb[half & 1], op.col[i] < lim ? o : kOOB, soff, dst + i * PP_RPI * ROWB);
+            load_lds16(r, op.col[i] < lim ? o : kOOB, soff, dst + i * PP_RPI * ROWB);
         }
     };
     bf16x8 fa[MF][2], fx[2][2], fy[2][2];  // [fragment][32-deep K step]
@@ -176,38 +195,44 @@ __device__ __forceinline__ void pp_loop(unsigned char* smem, const PPOperands& o
     };
     // B half 0 of tile kt is in x at the start; x holds B half 0 and y B half
     // 1 of the tile, and y B half 0 of the next tile at the end
-    auto tile = [&](int kt, bf16x8 (&x)[2][2], bf16x8 (&y)[2][2]) {
+    auto tile = [&](int kt, bf16x8 (&x)[2][2], bf16x8 (&y)[2][2], auto may_end) {
         read_a(0, kt);
-        request(1, kt + 1);
+        request(1, kt + 1, may_end);
         multiply(acc[0][0], x);
         read_b(1, kt, y);
-        request(2, kt + 2);
+        request(2, kt + 2, may_end);
         multiply(acc[0][1], y);
         read_a(1, kt);
-        request(0, kt + 2);
+        request(0, kt + 2, may_end);
         multiply(acc[1][1], y);
         read_b(0, kt + 1, y);
-        request(3, kt + 2);
+        request(3, kt + 2, may_end);
         multiply(acc[1][0], x);
     };
-    request(2, 0);
-    request(0, 0);
-    request(3, 0);
-    request(1, 0);
-    request(2, 1);
-    request(0, 1);
-    request(3, 1);
+    constexpr std::true_type end{};
+    request(2, 0, end);
+    request(0, 0, end);
+    request(3, 0, end);
+    request(1, 0, end);
+    request(2, 1, end);
+    request(0, 1, end);
+    request(3, 1, end);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(5 * PP_ND));  // B0 and A0 of tile 0 are in
     barrier_no_fence();
     if (wm == 1) barrier_no_fence();  // the lagging waves; the leading ones wait at the end
     __builtin_amdgcn_sched_barrier(0);
     read_b(0, 0, fx);
     int kt = 0;
+    if constexpr (kTail)  // the pairs of tiles whose requests stay before the end
+        for (; kt + 3 < nk; kt += 2) {
+            tile(kt, fx, fy, std::false_type{});
+            tile(kt + 1, fy, fx, std::false_type{});
+        }
     for (; kt + 1 < nk; kt += 2) {
-        tile(kt, fx, fy);
-        tile(kt + 1, fy, fx);
+        tile(kt, fx, fy, end);
+        tile(kt + 1, fy, fx, end);
     }
-    if (kt < nk) tile(kt, fx, fy);
+    if (kt < nk) tile(kt, fx, fy, end);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0) & kWaitLgkm0);
     if (wm == 0) barrier_no_fence();
     __builtin_amdgcn_sched_barrier(0);

@@ -4,8 +4,12 @@ and without a remainder, and channel counts around the tile's 128 channels."""
 import numpy as np
 import pytest
 
+import oracle
+from paper_2606_27866_amd import flexmoe as fm
 from paper_2606_27866_amd import synth
 from tests.gpu_util import BF16_TOL, GpuLayer, check_route, check_y, mini_layer, oracle_ref, say
+from tests.test_action_gpu import BWD_TOL, check_max
+from tests.test_saliency_gpu import check_scores
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +40,37 @@ def test_segment_and_reduction_edges(d, I_s, keep):
     assert rr["counts"].tolist() == ROWS
     check_route(r, rr)
     check_y(y, ref, BF16_TOL)
+
+
+@pytest.mark.parametrize("d,I,I_s", [(72, 264, 0), (320, 136, 136)])
+def test_backward_segment_and_reduction_edges(d, I, I_s):
+    """The training and saliency backward over the same segments: their row
+    counts are also the weight gradients' reduction lengths (1 to 9 K tiles)."""
+    import torch
+    say("backward edges d", d, "I", I, "I_s", I_s)
+    E, T = len(ROWS), sum(ROWS)
+    cfg, x, _, w, s = mini_layer("edges", T, d, E, I, 1, I_s, norm=0, config_id=92)
+    lg = skewed_logits(ROWS, d)
+    keep = np.minimum(np.array(KEEP, np.int32), I)
+    tgt = synth.make_target(cfg, T)
+    layer = fm.Layer(d, E, I, 1, I_s, synth.BF16, 0, max_tokens=T)
+    layer.set_weights(*[fm.to_device(a) if a is not None else None for a in (*w, *s)])
+    xd, ld = fm.to_device(x), fm.to_device(lg)
+
+    learner = fm.ActionLearner(layer, T, synth.ACTION_RATIOS)
+    learner.transpose_weights()
+    y = learner.forward(xd, ld, keep=fm.to_device(keep))
+    y_ref = oracle.layer_forward(x, lg, *w, keep, 1, 0, *s)
+    check_y(synth.bf16_bits_to_f32(fm.to_host(y)).astype(np.float64), y_ref, BF16_TOL)
+    dy = (y_ref - tgt).astype(np.float32)
+    dx, _, dm = learner.backward(ld, fm.to_device(dy))
+    torch.cuda.synchronize()
+    dx_ref, _, dm_ref = oracle.masked_backward(x, lg, *w, keep, 1, 0, dy, *s)
+    check_max(dx.cpu().numpy(), dx_ref, BWD_TOL, "dx")
+    for e in range(E):
+        check_max(dm.cpu().numpy()[e], dm_ref[e], BWD_TOL, "dmask[%d]" % e)
+
+    sal = fm.Saliency(layer, T)
+    sal.add_batch(xd, ld, fm.to_device(tgt))
+    torch.cuda.synchronize()
+    check_scores(sal.scores.cpu().numpy(), oracle.channel_saliency([(x, lg, tgt)], *w, 1, 0, *s))
