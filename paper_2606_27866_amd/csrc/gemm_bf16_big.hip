@@ -57,12 +57,11 @@ static_assert(128 * TROW * 2 <= PP_SMEM, "the staging tile fits in the operand s
 
 template <int MF>
 __device__ __forceinline__ void train_store_h_transposed(const Gemm1Params<bf16_t>& p, const SegMeta& sm,
-                                                         const PPAcc<MF>& acc, unsigned char* smem, int mtile,
-                                                         int ntile, int wave, int lane) {
+                                                         const PPAcc<MF>& acc, unsigned char* smem, int row0,
+                                                         int tile_rows, int ntile, int wave, int lane) {
     const int wm = wave >> 2, wn = wave & 3;
     bf16_t* st = reinterpret_cast<bf16_t*>(smem);
-    const int tile_rows = sm.rows - mtile * BM;            // real rows of this tile
-    const int pvalid = packed_width(sm.rows) - mtile * BM;  // rows written (padding included)
+    const int pvalid = packed_width(tile_rows);  // rows written: the segment's last tile pads it to 8
     const int ch_tile = ntile * (BN / 2);
     // the operand stages are free once no wave has requests in flight
     barrier_no_fence();
@@ -82,7 +81,7 @@ __device__ __forceinline__ void train_store_h_transposed(const Gemm1Params<bf16_
                 }
         }
     __syncthreads();
-    bf16_t* out = p.ht + (size_t)sm.prow0 + mtile * BM;
+    bf16_t* out = p.ht + (size_t)sm.prow0 + row0;
     for (int k = threadIdx.x; k < (BN / 2) * (BM / 8); k += THREADS) {
         const int cl = k / (BM / 8), r0 = (k % (BM / 8)) * 8;
         const int ch = ch_tile + cl;
@@ -137,7 +136,8 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
     // Masked rows (outside the segment, channels at or past k_e, columns past
     // d) get an offset past the descriptor's extent, for which the load
     // returns zeros.
-    const int tile_rows = min(BM, sm.rows - mtile * BM);
+    const int row_step = pp_row_step(sm.rows), row0 = mtile * row_step;
+    const int tile_rows = min(row_step, sm.rows - row0);
     const int mf = pp_mf(tile_rows);
     PPOperands op;
 #pragma unroll
@@ -167,7 +167,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int i = 0; i < PP_ND; ++i) {
-                tok[h][i] = mtile * BM + arow[h][i];
+                tok[h][i] = row0 + arow[h][i];
                 if (!shared) tok[h][i] = p1.perm[sm.row0 + min(tok[h][i], sm.rows - 1)];
             }
 #pragma unroll
@@ -197,7 +197,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
 #pragma unroll
             for (int i = 0; i < PP_ND; ++i) {
                 const int c = op.col[i];
-                const int row = mtile * BM + arow[h][i];
+                const int row = row0 + arow[h][i];
                 op.aoff[h][i] = aval[h][i] ? (uint32_t)(((size_t)row * ldh + c) * 2) : kOOB;
                 const int n = ntile * BN + h * PP_HALF_ROWS + pp_lds_row(wave, lane, i);
                 op.boff[h][i] = n < d ? (uint32_t)(((size_t)n * ldw + c) * 2) : kOOB;
@@ -235,7 +235,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
             for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
                 for (int i = 0; i < MF; ++i) {
-                    const int row = mtile * BM + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
+                    const int row = row0 + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
                     if (row >= sm.rows) continue;
                     bf16_t* hr = Hb + (size_t)row * ldh;
 #pragma unroll
@@ -259,7 +259,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
                 // [c][prow0 + row], zero in the rows up to the segment's padded
                 // height, staged through LDS as a [128 channels][256 rows] tile
                 // so that global stores are whole 16-byte row pieces
-                if (!shared) train_store_h_transposed<MF>(p1, sm, acc, smem, mtile, ntile, wave, lane);
+                if (!shared) train_store_h_transposed<MF>(p1, sm, acc, smem, row0, tile_rows, ntile, wave, lane);
             }
         } else {
             bf16_t* Ob = shared ? p2.Os + (size_t)split * p2.tokens * d : p2.O + (size_t)sm.row0 * d;
@@ -267,7 +267,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
             for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
                 for (int i = 0; i < MF; ++i) {
-                    const int row = mtile * BM + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
+                    const int row = row0 + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
                     if (row >= sm.rows) continue;
                     bf16_t* orow = Ob + (size_t)row * d;
 #pragma unroll

@@ -244,14 +244,16 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void dgrad_kernel(ActDg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int wm = wave >> 2, wn = wave & 3;
 
-    const int mf = pp_mf(sm.rows - mtile * BM);
+    const int row_step = pp_row_step(sm.rows), row0 = mtile * row_step;
+    const int tile_rows = min(row_step, sm.rows - row0);
+    const int mf = pp_mf(tile_rows);
     PPOperands op;
     op.K = p.d;
     const bf16_t* A = shared ? p.dYs : p.dO + (size_t)sm.row0 * p.d;
     const bf16_t* B = shared ? p.wsdt : p.wdt + (size_t)sm.e * p.I * p.d;
     op.ra = make_rsrc(A, (size_t)sm.rows * p.d);
     op.rb[0] = op.rb[1] = make_rsrc(B, (size_t)C * p.d);
-    nt_a_rows(wave, lane, mtile * BM, sm.rows, p.d, mf, op);
+    nt_a_rows(wave, lane, row0, sm.rows, p.d, mf, op);
     nt_b_rows(wave, lane, ntile * BN, C, p.d, op);
 
     const size_t rbase = shared ? 0 : (size_t)sm.row0;
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void dgrad_kernel(ActDg
     const int kk8 = min(packed_width(kk), C);    // dG/dU columns the dx GEMM reads
     bf16_t* stg = reinterpret_cast<bf16_t*>(smem);
     bf16_t* stu = stg + (kMode == 2 ? BM * DG_PITCH : (BN / 2) * DG_TPITCH);
-    pp_by_rows(sm.rows - mtile * BM, [&](auto tag) {
+    pp_by_rows(tile_rows, [&](auto tag) {
         constexpr int MF = decltype(tag)::value;
         PPAcc<MF> acc;
         pp_loop<MF, false>(smem, op, wave, lane, acc, PPZeroTail{});
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void dgrad_kernel(ActDg
 #pragma unroll
             for (int i = 0; i < MF; ++i) {
                 const int row = pp_frag_row<MF>(ah, wm, i) + (lane & 15);  // row of the tile
-                const int grow = mtile * BM + row;                         // row of the segment
+                const int grow = row0 + row;                         // row of the segment
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int cl = pp_frag_col(0, wn, j) + (lane >> 4) * 4;  // staged column of this half
@@ -325,17 +327,17 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void dgrad_kernel(ActDg
             if constexpr (kMode == 2) {
                 for (int k = threadIdx.x; k < BM * (BN / 2 / 8); k += THREADS) {
                     const int row = k / (BN / 2 / 8), cl = (k % (BN / 2 / 8)) * 8;
-                    const int grow = mtile * BM + row;
+                    const int grow = row0 + row;
                     const int c = ntile * BN + bh * PP_HALF_ROWS + cl;
-                    if (grow >= sm.rows || c >= kk8) continue;
+                    if (row >= tile_rows || c >= kk8) continue;
                     const size_t o = (rbase + grow) * (size_t)C + c;
                     *reinterpret_cast<u32x4*>(dG + o) = *reinterpret_cast<const u32x4*>(stg + row * DG_PITCH + cl);
                     *reinterpret_cast<u32x4*>(dU + o) = *reinterpret_cast<const u32x4*>(stu + row * DG_PITCH + cl);
                 }
             } else {
                 // rows up to the segment's padded height (zeros past its rows)
-                const int pvalid = packed_width(sm.rows) - mtile * BM;
-                const size_t col = (size_t)sm.prow0 + mtile * BM;
+                const int pvalid = packed_width(tile_rows);
+                const size_t col = (size_t)sm.prow0 + row0;
                 for (int k = threadIdx.x; k < (BN / 2) * (BM / 8); k += THREADS) {
                     const int cl = k / (BM / 8), r0 = (k % (BM / 8)) * 8;
                     const int c = ntile * BN + bh * PP_HALF_ROWS + cl;
@@ -389,7 +391,9 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void act_dx_kernel(ActD
     const int wm = wave >> 2, wn = wave & 3;
     const size_t rbase = shared ? 0 : (size_t)sm.row0;
 
-    const int mf = pp_mf(sm.rows - mtile * BM);
+    const int row_step = pp_row_step(sm.rows), row0 = mtile * row_step;
+    const int tile_rows = min(row_step, sm.rows - row0);
+    const int mf = pp_mf(tile_rows);
     PPOperands op;
     op.K = sm.kk;
     const bf16_t* Ag = (shared ? p.dGs : p.dG) + rbase * C;
@@ -397,10 +401,10 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void act_dx_kernel(ActD
     const bf16_t* Bg = shared ? p.wsgt : p.wgt + (size_t)sm.e * p.d * p.I;
     const bf16_t* Bu = shared ? p.wsut : p.wut + (size_t)sm.e * p.d * p.I;
     const PPSecond pairs{Ag, Au, Bg, Bu, (size_t)sm.rows * C, (size_t)p.d * C};
-    nt_a_rows(wave, lane, mtile * BM, sm.rows, C, mf, op);
+    nt_a_rows(wave, lane, row0, sm.rows, C, mf, op);
     nt_b_rows(wave, lane, ntile * BN, p.d, C, op);
     float* out = (shared ? p.dXs : p.dXr) + rbase * p.d;
-    pp_by_rows(sm.rows - mtile * BM, [&](auto tag) {
+    pp_by_rows(tile_rows, [&](auto tag) {
         constexpr int MF = decltype(tag)::value;
         PPAcc<MF> acc;
         pp_loop<MF, false>(smem, op, wave, lane, acc, PPZeroTail{}, pairs);
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void act_dx_kernel(ActD
         for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
             for (int i = 0; i < MF; ++i) {
-                const int row = mtile * BM + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
+                const int row = row0 + pp_frag_row<MF>(ah, wm, i) + (lane & 15);
                 if (row >= sm.rows) continue;
 #pragma unroll
                 for (int bh = 0; bh < 2; ++bh)

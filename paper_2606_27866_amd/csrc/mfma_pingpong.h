@@ -87,6 +87,16 @@ __device__ __forceinline__ int pp_col(int wave, int lane, int i) {
 // halves of 32*mf rows cover them.
 __device__ __forceinline__ int pp_mf(int rows) { return min(4, (rows + 63) >> 6); }
 
+// Rows per row tile of a segment of `rows` rows: its ceil(rows / 256) row
+// tiles take equal shares, rounded up to the 64-row steps of the MFMA work.
+// 273 rows go as 192 + 81 (3 + 2 steps) where 256 + 17 (4 + 1) cost as much
+// MFMA work and left one tile twice as long as the rest (a tile's requests,
+// prologue and epilogue do not shrink with its rows).
+__device__ __forceinline__ int pp_row_step(int rows) {
+    const int mt = ceil_div(rows, PP_BM);
+    return ceil_div(ceil_div(rows, mt), 64) * 64;
+}
+
 // Tile row of LDS row r of A half h (valid below 32*mf).
 __device__ __forceinline__ int pp_a_row(int h, int r, int mf) { return h * 32 * mf + r; }
 
