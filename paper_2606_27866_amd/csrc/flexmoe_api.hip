@@ -530,6 +530,20 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // kernel family: weight streaming for decode-sized T, large MFMA tiles
     // otherwise (bf16); LDS-tiled FMA for fp32
     const bool decode = bf16 && T <= kDecodeMaxT && !train;
+    // The shared expert's GEMMs run on the side stream (see below) for
+    // decode-sized batches and while its gate/up GEMM has few prefill tiles.
+    const bool side_ok = allow_side && has_shared && !train;
+    const bool sh_few = (long long)ceil_div(T, bf16 ? kBigBM1 : kF32BM) *
+                            ceil_div(D.I_shared, bf16 ? kBigBN1 : kF32BN) < (long long)kSideWaves * kComputeUnits;
+    const bool use_side = side_ok && (decode || sh_few);
+    // The routed experts' tile shape between decode and prefill.  The shared
+    // expert keeps the large tiles in its side-stream launches; in one launch
+    // over all segments its tiles are the routed ones, which suits it while
+    // they are few (no-allocation forward, 60 % of the channels, large tiles
+    // -> small: Qwen2-57B shape at 80 and 230 tokens 489 -> 444 and 536 -> 529
+    // us, Qwen1.5-MoE shape at 100, 300 and 1000 155 -> 134, 171 -> 163 and
+    // 252 -> 246).
+    const bool mid = bf16 && !decode && !train && sh_few && mid_tiles(T, D.top_k, D.E, D.I, kComputeUnits);
     const int ks2 = train ? 0 : shared_ks2(D, T);
     const int parts = train ? (has_shared ? 1 : 0) : shared_parts(D, T);
     if (train == 2) {
@@ -556,14 +570,17 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     const int dbn = wide_rt ? kDecWideBN : kDecBN;
     const TileShape ts = !bf16   ? TileShape{kF32BM, kF32BN, kF32BM, kF32BN, 0}
                          : decode ? TileShape{kDecodeMaxT, dbn, kDecodeMaxT, dbn, ks2}
+                         : mid    ? TileShape{kMidBM, kMidBN1, kMidBM, kMidBN2, ks2}
                                   : TileShape{kBigBM1, kBigBN1, kBigBM2, kBigBN2, ks2};
     // The shared expert's tile width.  On the side stream (every decode-sized
     // batch that may use it) its launches count their own tiles, of the
     // wide shape from kDecodeWideSharedT tokens on; in the launches over all
     // segments its tiles are those the dispatch counts, of the routed shape.
-    const bool side_ok = allow_side && has_shared && !train;
-    const bool sh_wide_tiles = side_ok && wide_sh;
-    const int sbn1 = sh_wide_tiles ? kDecWideBN : ts.bn1, sbn2 = sh_wide_tiles ? kDecWideBN : ts.bn2;
+    const bool sh_big_tiles = use_side && mid;
+    const bool sh_wide_tiles = use_side && wide_sh;
+    const int sbm1 = sh_big_tiles ? kBigBM1 : ts.bm1, sbm2 = sh_big_tiles ? kBigBM2 : ts.bm2;
+    const int sbn1 = sh_wide_tiles ? kDecWideBN : sh_big_tiles ? kBigBN1 : ts.bn1;
+    const int sbn2 = sh_wide_tiles ? kDecWideBN : sh_big_tiles ? kBigBN2 : ts.bn2;
 
     hipError_t err;
     // grid upper bounds from host-known sizes: the routed part's from the
@@ -572,20 +589,18 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     const long long rt2 = routed_row_tiles_ub(T, D.E, D.top_k, ts.bm2);
     const long long g1r = rt1 * ceil_div(D.I, ts.bn1);
     const long long g2r = rt2 * ceil_div(D.d, ts.bn2);
-    const long long g1s = has_shared ? (long long)ceil_div(T, ts.bm1) * ceil_div(D.I_shared, sbn1) : 0;
-    const long long g2s = has_shared ? (long long)ceil_div(T, ts.bm2) * ceil_div(D.d, sbn2) * parts : 0;
+    const long long g1s = has_shared ? (long long)ceil_div(T, sbm1) * ceil_div(D.I_shared, sbn1) : 0;
+    const long long g2s = has_shared ? (long long)ceil_div(T, sbm2) * ceil_div(D.d, sbn2) * parts : 0;
     if (g1r + g1s > 0x7fffffffLL || g2r + g2s > 0x7fffffffLL) return fail(FLEXMOE_ESHAPE, "tile grid too large");
 
     // The two GEMMs over one part of the tile list (n1, n2 workgroups), on
     // one stream.
-    // the shared expert's GEMMs on the side stream (see below)
-    const bool use_side = side_ok && (decode || g1s < (long long)kSideWaves * kComputeUnits);
-
     auto gemms = [&](int part, int seg_lo, int seg_hi, long long n1, long long n2, hipStream_t st) -> int {
         const bool sh = part == kPartShared;
         const int k1 = sh ? FLEXMOE_K_GATE_UP_SHARED : FLEXMOE_K_GATE_UP;
         const int k2 = sh ? FLEXMOE_K_DOWN_SHARED : FLEXMOE_K_DOWN;
         const bool wide = sh ? wide_sh : wide_rt;
+        const bool mid_part = mid && !sh;
         hipError_t e;
         if (bf16) {
             Gemm1Params<bf16_t> p1{(const bf16_t*)x, (const bf16_t*)w_gate_r, (const bf16_t*)w_up_r,
@@ -606,6 +621,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                     : decode     ? launch_gemm1_decode(p1, (int)n1, st)
                     : train == 1 ? launch_gemm1_big_train(p1, (int)n1, st)
                     : train == 2 ? launch_gemm1_big_train_rm(p1, (int)n1, st)
+                    : mid_part ? launch_gemm1_mid(p1, (int)n1, st)
                                  : launch_gemm1_big(p1, (int)n1, st, !use_side);
             }
             if (e != hipSuccess) return hip_fail(e, "gate/up GEMM launch");
@@ -621,6 +637,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                 KernelTimer kt(k2, st);
                 e = wide     ? launch_gemm2_decode_wide(p2, (int)n2, st)
                     : decode ? launch_gemm2_decode(p2, (int)n2, st)
+                    : mid_part ? launch_gemm2_mid(p2, (int)n2, st)
                              : launch_gemm2_big(p2, (int)n2, st);
             }
             if (e != hipSuccess) return hip_fail(e, "down GEMM launch");

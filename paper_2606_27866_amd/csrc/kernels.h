@@ -141,6 +141,7 @@ __device__ __forceinline__ bool tile_of(const P& p, int L, int& s, SegMeta& sm, 
 // with these numbers).
 constexpr int kF32BM = 64, kF32BN = 64;
 constexpr int kBigBM1 = 256, kBigBN1 = 128, kBigBM2 = 256, kBigBN2 = 256;
+constexpr int kMidBM = 128, kMidBN1 = 64, kMidBN2 = 128;
 constexpr int kDecodeMaxT = 64;     // T at or below which the weight-streaming kernels run
 constexpr int kGemvMaxT = 8;        // T at or below which the routed experts' weight-streaming
                                     // GEMMs run on the vector ALUs, in tiles of kDecBN channels /
@@ -152,6 +153,24 @@ constexpr int kDecodeWideSharedT = 5;  // above this many tokens the shared expe
                                        // tiles too
 constexpr int kSharedSplit2T = 16;  // above this many (decode) tokens the shared expert's down
                                     // reduction is split into chunks of 2 I channels, else of I
+
+// Whether the routed experts of a bf16 forward of T > kDecodeMaxT tokens take
+// the 128 x 128 tiles (gemm_mid.hip) rather than the 256 x 256 ones, from the
+// mean rows of an expert, n = T top_k / E:
+//   n <= kMidRows: streaming weights bounds the layer (at 60 % of the channels,
+//     small against large tiles: Qwen2-57B shape, n = 10 / 38 / 48, 420 / 529 /
+//     562 us against 491 / 585 / 602; n = 75: 695 against 678);
+//   n <= kMidRowsFew while the large tiles of the full width would number
+//     fewer than kMidWaves per compute unit, so that their last wave is a large
+//     part of the launch (Qwen1.5-MoE shape, n = 68 / 100: 215 / 266 us against
+//     242 / 308; Mixtral shape, n = 100: 437 against 512; past that, n = 137
+//     and 150, the two are equal).
+constexpr int kMidRows = 48, kMidRowsFew = 128, kMidWaves = 4;
+inline bool mid_tiles(int T, int top_k, int E, int I, int compute_units) {
+    const long long A = (long long)T * top_k;
+    if (A <= (long long)kMidRows * E) return true;
+    return A <= (long long)kMidRowsFew * E && (long long)E * ceil_div(I, kBigBN1) < (long long)kMidWaves * compute_units;
+}
 
 __global__ void route_kernel(const float* logits, int T, int E, int k, int norm_topk, int32_t* idx,
                              float* wts, int32_t* blockcnt, int NB);
@@ -182,6 +201,10 @@ __global__ void set_keep_kernel(int32_t* keep, KeepArgs t, int E);
 // alone (gate/up): no side-stream launch runs beside it.
 hipError_t launch_gemm1_big(const Gemm1Params<bf16_t>& p, int grid, hipStream_t s, bool alone);
 hipError_t launch_gemm2_big(const Gemm2Params<bf16_t>& p, int grid, hipStream_t s);
+// Between decode and prefill (mid_tiles): 128 x 128 tiles, two workgroups per
+// compute unit (gemm_mid.hip).
+hipError_t launch_gemm1_mid(const Gemm1Params<bf16_t>& p, int grid, hipStream_t s);
+hipError_t launch_gemm2_mid(const Gemm2Params<bf16_t>& p, int grid, hipStream_t s);
 // T <= kGemvMaxT: 16-wide tiles on the vector ALUs (gemv_decode.hip).
 hipError_t launch_gemm1_decode(const Gemm1Params<bf16_t>& p, int tiles, hipStream_t s);
 hipError_t launch_gemm2_decode(const Gemm2Params<bf16_t>& p, int tiles, hipStream_t s);

@@ -13,8 +13,8 @@ from tests.test_saliency_gpu import check_scores
 
 pytestmark = pytest.mark.gpu
 
-ROWS = [1, 63, 64, 65, 127, 128, 129, 191, 193, 255, 256, 257, 513]
-KEEP = [1, 7, 8, 63, 64, 65, 127, 128, 129, 192, 255, 256, 264]
+ROWS = [1, 63, 64, 65, 127, 128, 129, 191, 193, 255, 256, 257, 273, 385, 513]
+KEEP = [1, 7, 8, 63, 64, 65, 127, 128, 129, 192, 255, 256, 264, 200, 100]
 
 
 def skewed_logits(rows, seed):
@@ -40,6 +40,37 @@ def test_segment_and_reduction_edges(d, I_s, keep):
     assert rr["counts"].tolist() == ROWS
     check_route(r, rr)
     check_y(y, ref, BF16_TOL)
+
+
+# around the 32-row steps and the 128-row tiles that batches of few rows per
+# expert take (mean 94 rows, 13 x 3 channel tiles)
+MID_ROWS = [1, 31, 32, 33, 64, 65, 95, 97, 127, 128, 129, 160, 257]
+
+
+@pytest.mark.parametrize("d,I_s,noalloc", [(64, 0, False), (72, 136, False), (136, 0, False), (200, 2056, False),
+                                           (264, 2056, True), (64, 72, True)])
+@pytest.mark.parametrize("keep", [KEEP[:13], KEEP[12::-1]])
+def test_small_tile_edges(d, I_s, noalloc, keep):
+    """noalloc: the shared expert's rows take the same tiles, with a split
+    down reduction (two chunks at I_s = 2056)."""
+    import torch
+    say("small-tile edges d", d, "I_s", I_s, "noalloc", noalloc, "keep", keep)
+    E, T = len(MID_ROWS), sum(MID_ROWS)
+    cfg, x, _, w, s = mini_layer("mid", T, d, E, 264, 1, I_s, config_id=95)
+    lg = skewed_logits(MID_ROWS, d)
+    keep = np.array(keep, np.int32)
+    ref, rr = oracle_ref(cfg, x, lg, w, s, keep)
+    assert rr["counts"].tolist() == MID_ROWS
+    g = GpuLayer(d, E, 264, 1, I_s, synth.BF16, cfg.norm_topk, T, *w, *s)
+    y, r = g.forward(x, lg, keep)
+    check_route(r, rr)
+    check_y(y, ref, BF16_TOL)
+    if noalloc:
+        L, yd = g.layer, torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+        fm.flexmoe_layer_forward_noalloc(L.desc, T, fm.to_device(x), fm.to_device(lg), L.w_gate, L.w_up, L.w_down,
+                                         L.keep, L.ws_gate, L.ws_up, L.ws_down, yd)
+        torch.cuda.synchronize()
+        check_y(synth.bf16_bits_to_f32(fm.to_host(yd)).astype(np.float64), ref, BF16_TOL)
 
 
 @pytest.mark.parametrize("d,I,I_s", [(72, 264, 0), (320, 136, 136)])
