@@ -533,8 +533,16 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // The shared expert's GEMMs run on the side stream (see below) for
     // decode-sized batches and while its gate/up GEMM has few prefill tiles.
     const bool side_ok = allow_side && has_shared && !train;
-    const bool sh_few = (long long)ceil_div(T, bf16 ? kBigBM1 : kF32BM) *
-                            ceil_div(D.I_shared, bf16 ? kBigBN1 : kF32BN) < (long long)kSideWaves * kComputeUnits;
+    const bool f32_matrix = !bf16 && f32_matrix_tiles(T, D.d, D.I, D.I_shared);
+    TileShape ts_f32{kF32BM, kF32BN, kF32BM, kF32BN, 0};
+    if (f32_matrix) {
+        const int bm1 = f32_rows_per_tile(T, D.E, D.top_k, has_shared,
+                                          ceil_div(has_shared ? D.I_shared : D.I, kF32MBN1), kComputeUnits);
+        const int bm2 = f32_rows_per_tile(T, D.E, D.top_k, has_shared, ceil_div(D.d, kF32MBN2), kComputeUnits);
+        ts_f32 = TileShape{bm1, kF32MBN1, bm2, kF32MBN2, 0};
+    }
+    const bool sh_few = (long long)ceil_div(T, bf16 ? kBigBM1 : ts_f32.bm1) *
+                            ceil_div(D.I_shared, bf16 ? kBigBN1 : ts_f32.bn1) < (long long)kSideWaves * kComputeUnits;
     const bool use_side = side_ok && (decode || sh_few);
     // The routed experts' tile shape between decode and prefill.  The shared
     // expert keeps the large tiles in its side-stream launches; in one launch
@@ -568,7 +576,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     const bool wide_sh = decode && T > kDecodeWideSharedT;
     const bool wide_rt = decode && T > kGemvMaxT;
     const int dbn = wide_rt ? kDecWideBN : kDecBN;
-    const TileShape ts = !bf16   ? TileShape{kF32BM, kF32BN, kF32BM, kF32BN, 0}
+    const TileShape ts = !bf16   ? ts_f32
                          : decode ? TileShape{kDecodeMaxT, dbn, kDecodeMaxT, dbn, ks2}
                          : mid    ? TileShape{kMidBM, kMidBN1, kMidBM, kMidBN2, ks2}
                                   : TileShape{kBigBM1, kBigBN1, kBigBM2, kBigBN2, ks2};
@@ -646,9 +654,10 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                                   (const float*)ws_gate, (const float*)ws_up, perm, seg, t1,
                                   (float*)(ws + L.H), (float*)(ws + L.Hs), D.d, D.I, D.I_shared, D.E,
                                   D.top_k, nseg, T, part, seg_lo, seg_hi, (int)g1s, clipped};
+            p1.bm = ts.bm1;
             {
                 KernelTimer kt(k1, st);
-                e = launch_gemm1_f32(p1, (int)n1, st);
+                e = launch_gemm1_f32(p1, (int)n1, st, f32_matrix);
             }
             if (e != hipSuccess) return hip_fail(e, "gate/up GEMM launch");
             Gemm2Params<float> p2{(const float*)(ws + L.H), (const float*)(ws + L.Hs),
@@ -656,9 +665,10 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                                   (float*)Os, D.d, D.I, D.I_shared, D.E, nseg, T, 0, part, seg_lo, seg_hi,
                                   (int)g2s, clipped};
             p2.order = ord2;
+            p2.bm = ts.bm2;
             {
                 KernelTimer kt(k2, st);
-                e = launch_gemm2_f32(p2, (int)n2, st);
+                e = launch_gemm2_f32(p2, (int)n2, st, f32_matrix);
             }
             if (e != hipSuccess) return hip_fail(e, "down GEMM launch");
         }

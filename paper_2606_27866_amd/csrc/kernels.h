@@ -47,6 +47,8 @@ struct Gemm1Params {
     T* U;
     T* Gs;
     T* Us;
+    // fp32 matrix-core tiles: rows per tile (32, 64 or 128)
+    int bm;
     // launch_gemm1_big_train only: the routed rows' activations h transposed --
     // element [c][prow0 + r] for row r of a segment -- with zeros in the rows
     // [rows, packed_width(rows)) of each segment.  Row stride ldt.
@@ -79,6 +81,7 @@ struct Gemm2Params {
     // shared expert first, then the routed experts by decreasing GEMM width:
     // the longest reductions start first, so the launch ends evenly.
     const int32_t* order = nullptr;
+    int bm = 0;                 // fp32 matrix-core tiles: rows per tile
 };
 
 // Where routed expert e's weights live.  Ranked layout (online clipping):
@@ -139,7 +142,17 @@ __device__ __forceinline__ bool tile_of(const P& p, int L, int& s, SegMeta& sm, 
 
 // Tile shapes of the kernel families (the dispatch kernel builds tile tables
 // with these numbers).
-constexpr int kF32BM = 64, kF32BN = 64;
+constexpr int kF32BM = 64, kF32BN = 64;                      // fp32 on the vector ALUs
+// fp32 on the matrix cores: at most kF32MBM rows (f32_rows_per_tile)
+constexpr int kF32MBM = 128, kF32MBN1 = 64, kF32MBN2 = 128;
+// Whether an fp32 forward of T tokens takes the matrix-core tiles: every
+// operand block one tile addresses must stay below 2^31 bytes (32-bit buffer
+// offsets); there is no other limit, and no size at which the vector-ALU
+// tiles were faster.
+inline bool f32_matrix_tiles(long long T, long long d, long long I, long long Is) {
+    const long long w = d > (I > Is ? I : Is) ? d : (I > Is ? I : Is), n = I > Is ? I : Is;
+    return T * w < (1LL << 29) && n * d < (1LL << 29);
+}
 constexpr int kBigBM1 = 256, kBigBN1 = 128, kBigBM2 = 256, kBigBN2 = 256;
 constexpr int kMidBM = 128, kMidBN1 = 64, kMidBN2 = 128;
 constexpr int kDecodeMaxT = 64;     // T at or below which the weight-streaming kernels run
@@ -197,6 +210,19 @@ __global__ void dispatch_small_kernel(const float* logits, int T, int E, int k, 
                                       int32_t* t1start, int32_t* t2start, int32_t* order2);
 __global__ void set_keep_kernel(int32_t* keep, KeepArgs t, int E);
 
+// Rows per fp32 matrix-core tile of a GEMM with `cols` column tiles: halved
+// from 128 to at least 32 while the segment with the most rows (the shared
+// expert's T, else the mean of the routed ones, all together) has fewer tiles
+// than the chip has compute units.  Its tiles are the longest of the launch: a
+// shared down projection of 500 rows and 5632 channels in 64 tiles took 420
+// us, in 256 tiles 247.
+inline int f32_rows_per_tile(int T, int E, int top_k, bool has_shared, int cols, int compute_units) {
+    const long long rows = has_shared ? T : ((long long)T * top_k + E - 1) / E, segs = has_shared ? 1 : E;
+    int bm = kF32MBM;
+    while (bm > 32 && segs * ((rows + bm - 1) / bm) * cols < compute_units) bm /= 2;
+    return bm;
+}
+
 // Launchers (defined next to their kernels).  Each returns the launch status.
 // alone (gate/up): no side-stream launch runs beside it.
 hipError_t launch_gemm1_big(const Gemm1Params<bf16_t>& p, int grid, hipStream_t s, bool alone);
@@ -212,8 +238,9 @@ hipError_t launch_gemm2_decode(const Gemm2Params<bf16_t>& p, int tiles, hipStrea
 // matrix cores (gemm_decode.hip).
 hipError_t launch_gemm1_decode_wide(const Gemm1Params<bf16_t>& p, int tiles, hipStream_t s);
 hipError_t launch_gemm2_decode_wide(const Gemm2Params<bf16_t>& p, int tiles, hipStream_t s);
-hipError_t launch_gemm1_f32(const Gemm1Params<float>& p, int grid, hipStream_t s);
-hipError_t launch_gemm2_f32(const Gemm2Params<float>& p, int grid, hipStream_t s);
+// matrix: f32_matrix_tiles, else 64 x 64 tiles on the vector ALUs.
+hipError_t launch_gemm1_f32(const Gemm1Params<float>& p, int grid, hipStream_t s, bool matrix);
+hipError_t launch_gemm2_f32(const Gemm2Params<float>& p, int grid, hipStream_t s, bool matrix);
 hipError_t launch_combine(const void* O, const void* Os, const int32_t* pos, const float* wts,
                           int T, int k, int d, int shared_parts, int dtype, void* y, hipStream_t s);
 hipError_t launch_rank_reorder(const float* scores, const void* wg, const void* wu,
