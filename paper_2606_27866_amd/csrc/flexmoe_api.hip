@@ -686,12 +686,19 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // The training forwards compute every routed channel (the routed GEMMs
     // alone fill the chip): one launch over all segments there (measured 2 %
     // faster than the split on the Qwen1.5 shape).
+    // With the 256 x 256 tiles, which take whole compute units, the fork
+    // follows the routing kernel (hundreds of tokens and more, whose workgroups
+    // would otherwise wait for the first tiles to end): Qwen1.5-MoE shape at
+    // 2048 and 4096 tokens 320 -> 315 and 487 -> 469 us, Qwen2-57B shape at 800
+    // 772 -> 749.  The smaller tiles and batches lose more than they gain
+    // (Qwen1.5-MoE shape at 100 and 1023 tokens 136 -> 153, 218 -> 224).
+    const bool fork_late = bf16 && !decode && !mid;
     SideStream* side = nullptr;
     std::unique_lock<std::mutex> side_lock;
     if (use_side) {
         if ((rc = side_stream(&side)) != FLEXMOE_OK) return rc;
         side_lock = std::unique_lock<std::mutex>(side->mu);
-        if ((err = hipEventRecord(side->fork, s)) != hipSuccess) return hip_fail(err, "fork record");
+        if (!fork_late && (err = hipEventRecord(side->fork, s)) != hipSuccess) return hip_fail(err, "fork record");
     }
 
     // Routing and dispatch on the caller's stream.  The first routing kernel
@@ -717,6 +724,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     }
 
     if (use_side) {
+        if (fork_late && (err = hipEventRecord(side->fork, s)) != hipSuccess) return hip_fail(err, "fork record");
         if ((err = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess)
             return hip_fail(err, "fork wait");
         if ((rc = gemms(kPartShared, 0, 0, g1s, g2s, side->stream)) != FLEXMOE_OK) return rc;
