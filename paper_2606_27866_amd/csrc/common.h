@@ -63,7 +63,7 @@ struct SegMeta {
                     // bucketed forward (the extra channels' activations are 0)
     int32_t e;      // routed expert id (-1: the shared expert)
     int32_t prow0;  // routed segments: first row in the padded row space, where
-                    // every segment takes packed_width(rows) rows (the column
+                    // every segment takes its rows rounded up (the column
                     // offset of the segment in transposed activation copies)
     int32_t rt0;    // routed segments: row tiles (of the gate/up tile height) of
                     // the routed segments before this one
@@ -80,6 +80,8 @@ struct TileShape {
     int32_t bm2, bn2;   // down GEMM: rows x output columns per tile
     int32_t ks2;        // > 0: the shared expert's down GEMM is split into
                         // reductions of ks2 channels (one tile set each)
+    int32_t pad = 8;    // rows a routed segment is rounded up to in the padded
+                        // row space (SegMeta::prow0); a multiple of 8
 };
 
 // Lane-shift building block of the wave scans: v of the lane DPP control

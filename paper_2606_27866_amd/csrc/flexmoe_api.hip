@@ -452,7 +452,7 @@ struct TrainKeep {
     int mode;
     bf16_t *G, *U, *Gs, *Us;  // fragment-blocked g, u
     bf16_t* ht;               // mode 1: transposed h
-    int ldt;
+    int ldt, pad;             // its row stride; rows a segment is rounded up to in it
     const float* y_target;    // mode 1
     float* dy;
 };
@@ -576,10 +576,11 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     const bool wide_sh = decode && T > kDecodeWideSharedT;
     const bool wide_rt = decode && T > kGemvMaxT;
     const int dbn = wide_rt ? kDecWideBN : kDecBN;
-    const TileShape ts = !bf16   ? ts_f32
+    TileShape ts = !bf16         ? ts_f32
                          : decode ? TileShape{kDecodeMaxT, dbn, kDecodeMaxT, dbn, ks2}
                          : mid    ? TileShape{kMidBM, kMidBN1, kMidBM, kMidBN2, ks2}
                                   : TileShape{kBigBM1, kBigBN1, kBigBM2, kBigBN2, ks2};
+    if (tr) ts.pad = tr->pad;
     // The shared expert's tile width.  On the side stream (every decode-sized
     // batch that may use it) its launches count their own tiles, of the
     // wide shape from kDecodeWideSharedT tokens on; in the launches over all
@@ -915,19 +916,21 @@ namespace {
 struct SalLayout {
     Layout f;  // the forward's regions (shared expert unsplit)
     size_t dy, dO, xt, dot, G, U, ht, dgt, dut, wdt, partial, total;
-    int ldt, nI, nM;
+    int pad, ldt, nI, nM;
 };
 
 // Row stride of the transposed activation copies: every routed segment takes
-// packed_width(rows) <= rows + 7 rows, so A + 7E bounds the padded total.
-long long sal_ldt(const flexmoe_layer_desc& D, int T) {
-    return ((long long)T * D.top_k + 7LL * D.E + 7) & ~7LL;
+// its rows rounded up to `pad`, so A + (pad - 1) E bounds the padded total.
+long long sal_ldt(const flexmoe_layer_desc& D, int T, int pad = 8) {
+    return ((long long)T * D.top_k + (pad - 1LL) * D.E + pad - 1) / pad * pad;
 }
 
-SalLayout sal_layout(const flexmoe_layer_desc& D, int T) {
+// with_wdt: room for the transposed down weights.
+SalLayout sal_carve(const flexmoe_layer_desc& D, int T, int pad, bool with_wdt) {
     SalLayout S{};
     S.f = layout(D, T, (size_t)T);
-    S.ldt = (int)sal_ldt(D, T);
+    S.pad = pad;
+    S.ldt = (int)sal_ldt(D, T, pad);
     S.nI = ceil_div(D.I, kSalTile);
     S.nM = ceil_div(D.d, kSalTile);
     const size_t A = (size_t)T * D.top_k, d = D.d, I = D.I, ldt = S.ldt;
@@ -947,10 +950,27 @@ SalLayout sal_layout(const flexmoe_layer_desc& D, int T) {
     S.ht = take(I * ldt * 2);
     S.dgt = take(I * ldt * 2);
     S.dut = take(I * ldt * 2);
-    S.wdt = take((size_t)D.E * I * d * 2);
+    if (with_wdt) S.wdt = take((size_t)D.E * I * d * 2);
     S.partial = take(3 * (size_t)D.E * I * S.nM * kSalWaveM * 4);
     S.total = off;
     return S;
+}
+
+// The layout whose size flexmoe_saliency_workspace_bytes reports.
+SalLayout sal_layout(const flexmoe_layer_desc& D, int T) { return sal_carve(D, T, 8, true); }
+
+// The layout of a call.  The weight-gradient GEMMs read 128-byte pieces of the
+// transposed copies' rows; segments that start on 64-row boundaries put each
+// in one cache line instead of two (wgrad, Qwen1.5-MoE shape with 4096 and
+// 16384 tokens 508 -> 454 and 1357 -> 1110 us, Mixtral shape with 2048 2815 ->
+// 2288).  The wider copies fit the reported size when the caller brings the
+// transposed down weights, whose room they then take, on all but the smallest
+// layers; otherwise segments keep their 8-row boundaries.
+SalLayout sal_layout_for(const flexmoe_layer_desc& D, int T, bool have_wdt) {
+    const SalLayout S = sal_layout(D, T);
+    if (!have_wdt || (long long)std::max(D.d, D.I) * sal_ldt(D, T, 64) >= (1LL << 30)) return S;
+    const SalLayout W = sal_carve(D, T, 64, false);
+    return W.total <= S.total ? W : S;
 }
 
 int check_saliency_shape(const flexmoe_layer_desc& D, int T) {
@@ -980,10 +1000,11 @@ int saliency_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, cons
     const bool has_shared = D.I_shared > 0;
     if (has_shared != (ws_gate && ws_up && ws_down) || (!has_shared && (ws_gate || ws_up || ws_down)))
         return fail(FLEXMOE_EINVAL, "shared weights must be given iff I_shared > 0");
-    const SalLayout S = sal_layout(D, T);
-    if (!workspace || workspace_bytes < S.total)
-        return fail(FLEXMOE_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, S.total);
+    const size_t need = sal_layout(D, T).total;
+    if (!workspace || workspace_bytes < need)
+        return fail(FLEXMOE_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace_bytes, need);
     if (((uintptr_t)workspace) & 255) return fail(FLEXMOE_EWORKSPACE, "workspace is not 256-byte aligned");
+    const SalLayout S = sal_layout_for(D, T, w_down_t != nullptr);
 
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
@@ -1020,7 +1041,7 @@ int saliency_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, cons
     set_keep_kernel<<<1, kMaxExperts, 0, s>>>(keep, ka, D.E);
     if ((err = hipGetLastError()) != hipSuccess) return hip_fail(err, "keep upload");
     static_assert(kBigBM1 == kSalTile, "segment row tiles (rt0) are counted in saliency tile rows");
-    const TrainKeep tk{1, G, U, nullptr, nullptr, ht, S.ldt, y_target, dy};
+    const TrainKeep tk{1, G, U, nullptr, nullptr, ht, S.ldt, S.pad, y_target, dy};
     rc = forward_impl(desc, T, x, logits, w_gate, w_up, w_down, keep, 0, 0x7fffffff, nullptr, 0, ws_gate, ws_up,
                       ws_down, nullptr, workspace, workspace_bytes, nullptr, stream, &tk);
     if (rc != FLEXMOE_OK) return rc;
@@ -1265,7 +1286,7 @@ int flexmoe_train_forward(const flexmoe_layer_desc* desc, int32_t T, const void*
     if ((rc = check_workspace(S, workspace, workspace_bytes)) != FLEXMOE_OK) return rc;
     TrainPtrs P = train_ptrs(S, workspace);
     static_assert(kBigBM1 == kTrainTile, "segment row tiles (rt0) are counted in training tile rows");
-    const TrainKeep tk{2, P.G, P.U, P.Gs, P.Us, nullptr, 0, nullptr, nullptr};
+    const TrainKeep tk{2, P.G, P.U, P.Gs, P.Us, nullptr, 0, 8, nullptr, nullptr};
     return forward_impl(desc, T, x, logits, w_gate, w_up, w_down, keep_dev, 0, 0x7fffffff, nullptr, 0, ws_gate,
                         ws_up, ws_down, y, workspace, workspace_bytes, nullptr, stream, &tk);
 }

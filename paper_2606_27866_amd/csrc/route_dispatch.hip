@@ -209,7 +209,7 @@ __device__ void write_tables(CountFn count, RankFn rank, const int* off, const i
                 m.ch0 = ch0[e];
                 m.kg = plan && m.kk > 0 ? min(max(plan[E + e], m.kk), I) : m.kk;
                 m.e = e;
-                n3 = packed_width(m.rows);
+                n3 = ceil_div(m.rows, ts.pad) * ts.pad;
                 n4 = ceil_div(m.rows, ts.bm1);
             }
             if (m.rows > 0 && m.kk > 0) {
