@@ -81,7 +81,7 @@ struct TileShape {
     int32_t ks2;        // > 0: the shared expert's down GEMM is split into
                         // reductions of ks2 channels (one tile set each)
     int32_t pad = 8;    // rows a routed segment is rounded up to in the padded
-                        // row space (SegMeta::prow0); a multiple of 8
+                        // row space (SegMeta::prow0): a power of two, at least 8
 };
 
 // Lane-shift building block of the wave scans: v of the lane DPP control

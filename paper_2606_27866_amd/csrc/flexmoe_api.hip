@@ -710,11 +710,8 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     if (small && !pre_routed) {
         // one workgroup routes and dispatches everything (timed as routing)
         KernelTimer kt(FLEXMOE_K_ROUTE, s);
-        dispatch_small_kernel<<<1, 64 * kSmallWaves, 0, s>>>(logits, T, D.E, D.top_k, D.norm_topk, keep_dev,
-                                                             D.I, D.I_shared, D.d, ts, packed_limit, plan, 0,
-                                                             idx, wts, counts, perm, pos, offsets, seg, t1,
-                                                             t2, ord2);
-        err = hipGetLastError();
+        err = launch_dispatch_small(logits, T, D.E, D.top_k, D.norm_topk, keep_dev, D.I, D.I_shared, D.d, ts,
+                                    packed_limit, plan, 0, idx, wts, counts, perm, pos, offsets, seg, t1, t2, ord2, s);
         if (err != hipSuccess) return hip_fail(err, "dispatch launch");
     } else {
         KernelTimer kt(FLEXMOE_K_ROUTE, s);
@@ -735,11 +732,8 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     if (pre_routed) {
         // the tokens are routed; one workgroup dispatches them
         KernelTimer kt(FLEXMOE_K_DISPATCH_SCATTER, s);
-        dispatch_small_kernel<<<1, 64 * kSmallWaves, 0, s>>>(logits, T, D.E, D.top_k, D.norm_topk, keep_dev,
-                                                             D.I, D.I_shared, D.d, ts, packed_limit, plan, 1,
-                                                             idx, wts, counts, perm, pos, offsets, seg, t1,
-                                                             t2, ord2);
-        err = hipGetLastError();
+        err = launch_dispatch_small(logits, T, D.E, D.top_k, D.norm_topk, keep_dev, D.I, D.I_shared, D.d, ts,
+                                    packed_limit, plan, 1, idx, wts, counts, perm, pos, offsets, seg, t1, t2, ord2, s);
         if (err != hipSuccess) return hip_fail(err, "dispatch launch");
     } else if (!small) {
         {

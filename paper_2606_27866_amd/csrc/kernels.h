@@ -202,12 +202,11 @@ __global__ void dispatch_scatter_kernel(const int32_t* idx, const int32_t* keep,
                                         int32_t* perm, int32_t* pos,
                                         int32_t* offsets, SegMeta* seg, int32_t* t1start,
                                         int32_t* t2start, int32_t* order2);
-__global__ void dispatch_small_kernel(const float* logits, int T, int E, int k, int norm_topk,
-                                      const int32_t* keep, int I, int I_shared, int d, TileShape ts,
-                                      int packed_limit, const int32_t* plan, int pre_routed, int32_t* idx,
-                                      float* wts, int32_t* counts,
-                                      int32_t* perm, int32_t* pos, int32_t* offsets, SegMeta* seg,
-                                      int32_t* t1start, int32_t* t2start, int32_t* order2);
+hipError_t launch_dispatch_small(const float* logits, int T, int E, int k, int norm_topk, const int32_t* keep, int I,
+                                 int I_shared, int d, TileShape ts, int packed_limit, const int32_t* plan,
+                                 int pre_routed, int32_t* idx, float* wts, int32_t* counts, int32_t* perm,
+                                 int32_t* pos, int32_t* offsets, SegMeta* seg, int32_t* t1start, int32_t* t2start,
+                                 int32_t* order2, hipStream_t s);
 __global__ void set_keep_kernel(int32_t* keep, KeepArgs t, int E);
 
 // Rows per fp32 matrix-core tile of a GEMM with `cols` column tiles: halved

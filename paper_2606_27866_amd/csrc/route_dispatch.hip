@@ -69,59 +69,120 @@ __device__ __forceinline__ void rank_keys(const RouteScratch& rs, const uint32_t
     }
 }
 
-// One wave routes one token whose logits are in v (load_logits): lane j < k
-// returns the j-th selected expert and its router weight.  Each lane ranks
-// its (up to four) experts by counting the experts ordered before them under
-// the order above, reading the token's keys back from LDS.  Ranks are a
+// The ranks of NT tokens at once.  kOnce: larger keys are counted with one
+// compare per pair; every pair of different keys adds one to the sum of all ranks, so
+// a sum below E (E - 1) / 2 tells that some keys are equal, and only then the
+// token is ranked again with the ids breaking ties.  Up to 16 experts the sum
+// costs more than the second compares (8 experts: 0.4 us of a 26 us forward).
+template <int NT, int NQ, bool kOnce>
+__device__ __forceinline__ void rank_tokens(const RouteScratch (&rs)[NT], const uint32_t (&mk)[NT][4], int E, int E8,
+                                            int lane, int (&rank)[NT][4]) {
+    if (!kOnce || E <= 16) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) rank_keys<NQ>(rs[t], mk[t], E8, lane, rank[t]);
+        return;
+    }
+    for (int j0 = 0; j0 < E8; j0 += 8) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const uint4 k0 = *reinterpret_cast<const uint4*>(&rs[t].key[j0]);
+            const uint4 k1 = *reinterpret_cast<const uint4*>(&rs[t].key[j0 + 4]);
+            const uint32_t o[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) rank[t][q] += o[i] > mk[t][q];
+        }
+    }
+    int sum[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        sum[t] = 0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sum[t] += lane + 64 * q < E ? rank[t][q] : 0;
+        sum[t] = lane63(wave_incl_scan(sum[t]));
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+        if (sum[t] != E * (E - 1) / 2) {  // wave-uniform
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) rank[t][q] = 0;
+            rank_keys<NQ>(rs[t], mk[t], E8, lane, rank[t]);
+        }
+}
+
+// One wave routes NT tokens whose logits are in v (load_logits): lane j < k
+// returns the j-th selected expert and its router weight of each.  Each lane
+// ranks its (up to four) experts by counting the experts ordered before them
+// under the order above, reading the token's keys back from LDS.  Ranks are a
 // permutation of 0..E-1, so the expert of rank j < k fills slot j -- the
 // top-k in order, with no chain of cross-lane steps.  The LDS row is padded
 // to a multiple of 8 with key 0 and ids at or past E, which no expert counts.
 // Softmax over all E experts, shifted by the largest logit; with norm_topk
-// the k weights are divided by their sum.
-__device__ __forceinline__ void route_token(const float (&v)[4], int E, int k, int norm_topk, int lane,
-                                            RouteScratch& rs, int& my_id, float& my_w) {
+// the k weights are divided by their sum.  A token's steps wait on one
+// another (LDS round trips, wave sums, expf): two tokens at a time fill each
+// other's waits.
+template <int NT, bool kOnce>
+__device__ __forceinline__ void route_tokens(const float (&v)[NT][4], int E, int k, int norm_topk, int lane,
+                                             RouteScratch (&rs)[NT], int (&my_id)[NT], float (&my_w)[NT]) {
     const int nq = ceil_div(E, 64);         // wave-uniform
     const int E8 = ceil_div(E, 8) * 8;      // <= kMaxExperts
-    uint32_t mk[4];
+    uint32_t mk[NT][4];
+    int rank[NT][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q;
-        mk[q] = route_key(v[q]);
-        if (e < E) rs.key[e] = mk[q];
-        else if (e < E8) rs.key[e] = 0u;
-    }
-    __builtin_amdgcn_wave_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    int rank[4] = {0, 0, 0, 0};
-    switch (nq) {
-        case 1: rank_keys<1>(rs, mk, E8, lane, rank); break;
-        case 2: rank_keys<2>(rs, mk, E8, lane, rank); break;
-        case 3: rank_keys<3>(rs, mk, E8, lane, rank); break;
-        default: rank_keys<4>(rs, mk, E8, lane, rank); break;
-    }
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q;
-        if (e < E && rank[q] < k) {
-            rs.slot_id[rank[q]] = e;
-            rs.slot_v[rank[q]] = v[q];
+        for (int q = 0; q < 4; ++q) {
+            const int e = lane + 64 * q;
+            mk[t][q] = route_key(v[t][q]);
+            rank[t][q] = 0;
+            if (e < E) rs[t].key[e] = mk[t][q];
+            else if (e < E8) rs[t].key[e] = 0u;
         }
-    }
     __builtin_amdgcn_wave_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    const float m = rs.slot_v[0];
-    my_id = lane < k ? rs.slot_id[lane] : 0;
-    const float my_logit = lane < k ? rs.slot_v[lane] : 0.0f;
-    __builtin_amdgcn_wave_barrier();  // the scratch is reused by the wave's next token
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    float z = 0.0f;
+    switch (nq) {
+        case 1: rank_tokens<NT, 1, kOnce>(rs, mk, E, E8, lane, rank); break;
+        case 2: rank_tokens<NT, 2, kOnce>(rs, mk, E, E8, lane, rank); break;
+        case 3: rank_tokens<NT, 3, kOnce>(rs, mk, E, E8, lane, rank); break;
+        default: rank_tokens<NT, 4, kOnce>(rs, mk, E, E8, lane, rank); break;
+    }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (lane + 64 * q < E) z += expf(v[q] - m);
-    z = wave_total_f(z);
-    float w = lane < k ? expf(my_logit - m) / z : 0.0f;
-    if (norm_topk) w = w / wave_total_f(w);
-    my_w = w;
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = lane + 64 * q;
+            if (e < E && rank[t][q] < k) {
+                rs[t].slot_id[rank[t][q]] = e;
+                rs[t].slot_v[rank[t][q]] = v[t][q];
+            }
+        }
+    __builtin_amdgcn_wave_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    float m[NT], my_logit[NT], z[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        m[t] = rs[t].slot_v[0];
+        my_id[t] = lane < k ? rs[t].slot_id[lane] : 0;
+        my_logit[t] = lane < k ? rs[t].slot_v[lane] : 0.0f;
+    }
+    __builtin_amdgcn_wave_barrier();  // the scratch is reused by the wave's next tokens
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        z[t] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (lane + 64 * q < E) z[t] += expf(v[t][q] - m[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) z[t] = wave_total_f(z[t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        float w = lane < k ? expf(my_logit[t] - m[t]) / z[t] : 0.0f;
+        if (norm_topk) w = w / wave_total_f(w);
+        my_w[t] = w;
+    }
 }
 
 // One wave: exclusive scan over experts of the active counts (k_e > 0, k_e
@@ -209,7 +270,7 @@ __device__ void write_tables(CountFn count, RankFn rank, const int* off, const i
                 m.ch0 = ch0[e];
                 m.kg = plan && m.kk > 0 ? min(max(plan[E + e], m.kk), I) : m.kk;
                 m.e = e;
-                n3 = ceil_div(m.rows, ts.pad) * ts.pad;
+                n3 = (m.rows + ts.pad - 1) & -ts.pad;
                 n4 = ceil_div(m.rows, ts.bm1);
             }
             if (m.rows > 0 && m.kk > 0) {
@@ -321,20 +382,20 @@ __global__ __launch_bounds__(64 * kRouteTokens) void route_kernel(
     const float* __restrict__ logits, int T, int E, int k, int norm_topk,
     int32_t* __restrict__ idx, float* __restrict__ wts, int32_t* __restrict__ blockcnt, int NB) {
     __shared__ int hist[kMaxExperts];
-    __shared__ RouteScratch rs[kRouteTokens];
+    __shared__ RouteScratch rs[kRouteTokens][1];
     for (int e = threadIdx.x; e < E; e += blockDim.x) hist[e] = 0;
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int t = blockIdx.x * kRouteTokens + wave;
     if (t < T) {  // uniform across the wave
-        int id;
-        float w, v[4];
-        load_logits(logits + (size_t)t * E, E, lane, v);
-        route_token(v, E, k, norm_topk, lane, rs[wave], id, w);
+        int id[1];
+        float w[1], v[1][4];
+        load_logits(logits + (size_t)t * E, E, lane, v[0]);
+        route_tokens<1, true>(v, E, k, norm_topk, lane, rs[wave], id, w);
         if (lane < k) {
-            idx[(size_t)t * k + lane] = id;
-            wts[(size_t)t * k + lane] = w;
-            atomicAdd(&hist[id], 1);  // a count: arrival order does not matter
+            idx[(size_t)t * k + lane] = id[0];
+            wts[(size_t)t * k + lane] = w[0];
+            atomicAdd(&hist[id[0]], 1);  // a count: arrival order does not matter
         }
     }
     __syncthreads();
@@ -423,6 +484,13 @@ __global__ __launch_bounds__(64) void dispatch_scatter_kernel(
 // in the same order as one pass over the tokens would.  With pre_routed the
 // tokens were routed by route_kernel (spread over several compute units):
 // the waves read their tokens' expert ids instead.
+// kPairs: the waves route their tokens two at a time and rank them with one
+// compare per pair of experts (more than one token per wave).  Steps of at
+// most 16 tokens keep a kernel without either: the pairs' code and LDS cost a
+// small layer 0.5 us there, and routing a Qwen2-57B-shaped single token 2 us
+// sooner made its step 2 us longer (121 -> 124): the routed gate/up GEMM then
+// contends with the shared expert's, whose chain ends last.
+template <bool kPairs>
 __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
     const float* __restrict__ logits, int T, int E, int k, int norm_topk,
     const int32_t* __restrict__ keep, int I, int I_shared, int d, TileShape ts, int packed_limit,
@@ -440,7 +508,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
     __shared__ int n2s[kMaxExperts + 1];
     __shared__ int ordl[kMaxExperts + 1];
     __shared__ int32_t sidx[kSmallAssign];
-    __shared__ RouteScratch rs[kSmallWaves];
+    __shared__ RouteScratch rs[kSmallWaves][kPairs ? 2 : 1];
     __shared__ int keep_s[kMaxExperts];
     __shared__ int part[kSmallWaves][kMaxExperts];  // per-wave partial counts of the width ranks
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -459,21 +527,47 @@ __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
             atomicAdd(&hist[wave][id], 1);  // a count: arrival order does not matter
         }
     }
-    // the next token's logits are loaded while this one is ranked
-    float vn[4];
-    if (!pre_routed && t0 < t1) load_logits(logits + (size_t)t0 * E, E, lane, vn);
-    for (int t = pre_routed ? t1 : t0; t < t1; ++t) {
-        int id;
-        float w, v[4];
+    if (!pre_routed) {
+        auto keep_token = [&](int t, int id, float w) {
+            if (lane < k) {
+                idx[(size_t)t * k + lane] = id;
+                wts[(size_t)t * k + lane] = w;
+                sidx[t * k + lane] = id;
+                atomicAdd(&hist[wave][id], 1);  // a count: arrival order does not matter
+            }
+        };
+        // two tokens at a time (T = 37 and 64, 60 experts: this kernel 17.9 ->
+        // 15.0 and 23.9 -> 17.9 us between events); the next pair's logits are
+        // loaded while this one is ranked
+        constexpr int NT = kPairs ? 2 : 1;
+        float vn[NT][4];
+        auto load_next = [&](int t) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = vn[q];
-        if (t + 1 < t1) load_logits(logits + (size_t)(t + 1) * E, E, lane, vn);
-        route_token(v, E, k, norm_topk, lane, rs[wave], id, w);
-        if (lane < k) {
-            idx[(size_t)t * k + lane] = id;
-            wts[(size_t)t * k + lane] = w;
-            sidx[t * k + lane] = id;
-            atomicAdd(&hist[wave][id], 1);  // a count: arrival order does not matter
+            for (int n = 0; n < NT; ++n) load_logits(logits + (size_t)min(t + n, T - 1) * E, E, lane, vn[n]);
+        };
+        if (t0 < t1) load_next(t0);
+        int t = t0;
+        if constexpr (kPairs)
+            for (; t + 1 < t1; t += 2) {
+                int id[2];
+                float w[2], v[2][4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    v[0][q] = vn[0][q];
+                    v[1][q] = vn[1][q];
+                }
+                if (t + 2 < t1) load_next(t + 2);
+                route_tokens<2, true>(v, E, k, norm_topk, lane, rs[wave], id, w);
+                keep_token(t, id[0], w[0]);
+                keep_token(t + 1, id[1], w[1]);
+            }
+        if (t < t1) {
+            int id[1];
+            float w[1], v[1][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[0][q] = vn[0][q];
+            route_tokens<1, kPairs>(v, E, k, norm_topk, lane, reinterpret_cast<RouteScratch(&)[1]>(rs[wave]), id, w);
+            keep_token(t, id[0], w[0]);
         }
     }
     __syncthreads();
@@ -522,6 +616,22 @@ __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
     // this wave's running position inside each expert starts at its base
     auto base = [&](int e) { return off[e]; };
     place(sidx, t0 * k, t1 * k, kk_s, hist[wave], base, perm, pos);
+}
+
+hipError_t launch_dispatch_small(const float* logits, int T, int E, int k, int norm_topk, const int32_t* keep, int I,
+                                 int I_shared, int d, TileShape ts, int packed_limit, const int32_t* plan,
+                                 int pre_routed, int32_t* idx, float* wts, int32_t* counts, int32_t* perm,
+                                 int32_t* pos, int32_t* offsets, SegMeta* seg, int32_t* t1start, int32_t* t2start,
+                                 int32_t* order2, hipStream_t s) {
+    if (T <= kSmallWaves || pre_routed)
+        dispatch_small_kernel<false><<<1, 64 * kSmallWaves, 0, s>>>(logits, T, E, k, norm_topk, keep, I, I_shared, d, ts,
+                                                                    packed_limit, plan, pre_routed, idx, wts, counts,
+                                                                    perm, pos, offsets, seg, t1start, t2start, order2);
+    else
+        dispatch_small_kernel<true><<<1, 64 * kSmallWaves, 0, s>>>(logits, T, E, k, norm_topk, keep, I, I_shared, d, ts,
+                                                                   packed_limit, plan, 0, idx, wts, counts, perm, pos,
+                                                                   offsets, seg, t1start, t2start, order2);
+    return hipGetLastError();
 }
 
 __global__ void set_keep_kernel(int32_t* __restrict__ keep, KeepArgs t, int E) {
