@@ -562,8 +562,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
             full.v[e] = e < D.E ? D.I : 0;
         }
         plan = (int32_t*)(ws + L.plan);
-        set_keep_kernel<<<1, kMaxExperts, 0, (hipStream_t)stream>>>(plan, order, D.E);
-        set_keep_kernel<<<1, kMaxExperts, 0, (hipStream_t)stream>>>(plan + D.E, full, D.E);
+        set_plan_kernel<<<1, kMaxExperts, 0, (hipStream_t)stream>>>(nullptr, plan, full, order, full, D.E);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "plan upload");
     }
@@ -634,14 +633,12 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                                  : launch_gemm1_big(p1, (int)n1, st, !use_side);
             }
             if (e != hipSuccess) return hip_fail(e, "gate/up GEMM launch");
-            // the masked layer's down GEMM reduces over the kept channels only
-            if (train == 2 && !sh && (e = launch_seg_use_kept(seg, nseg, st)) != hipSuccess)
-                return hip_fail(e, "segment width launch");
             Gemm2Params<bf16_t> p2{(const bf16_t*)(ws + L.H), (const bf16_t*)(ws + L.Hs),
                                    (const bf16_t*)w_down_r, (const bf16_t*)ws_down, seg, t2, (bf16_t*)O,
                                    (bf16_t*)Os, D.d, D.I, D.I_shared, D.E, nseg, T, ks2, part, seg_lo,
                                    seg_hi, (int)g2s, clipped};
             p2.order = ord2;
+            p2.kept_only = train == 2;
             {
                 KernelTimer kt(k2, st);
                 e = wide     ? launch_gemm2_decode_wide(p2, (int)n2, st)

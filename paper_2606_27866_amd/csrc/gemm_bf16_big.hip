@@ -183,7 +183,7 @@ __device__ __forceinline__ void big_tile(const Gemm1Params<bf16_t>& p1, const Ge
             }
     } else {
         const int kbeg = shared && p2.ks2 > 0 ? split * p2.ks2 : 0;
-        op.K = shared && p2.ks2 > 0 ? min(sm.kg - kbeg, p2.ks2) : sm.kg;
+        op.K = shared && p2.ks2 > 0 ? min(sm.kg - kbeg, p2.ks2) : p2.kept_only ? sm.kk : sm.kg;
         const RoutedWeights rw = shared ? RoutedWeights{0, 0, p2.Is} : routed_weights(p2, sm);
         const int ldh = shared ? p2.Is : p2.I;  // H row stride
         const int ldw = rw.ldd;                 // W_down row stride

@@ -82,6 +82,9 @@ struct Gemm2Params {
     // the longest reductions start first, so the launch ends evenly.
     const int32_t* order = nullptr;
     int bm = 0;                 // fp32 matrix-core tiles: rows per tile
+    // training forward (prefill tiles): reduce over the kept channels kk, not
+    // over the GEMM width kg, which is I there
+    int kept_only = 0;
 };
 
 // Where routed expert e's weights live.  Ranked layout (online clipping):
@@ -194,6 +197,7 @@ __global__ void dispatch_scan_kernel(const int32_t* blockcnt, int NB, int32_t* b
 // k_e = 0 (the ranked layout passes INT32_MAX).  `plan` (NULL: experts in id
 // order, GEMM width = k_e): the bucketed forward's segment order plan[0..E)
 // (expert ids) and GEMM widths plan[E..2E).
+// keep = NULL: the plan alone
 __global__ void set_plan_kernel(int32_t* keep, int32_t* plan, KeepArgs k, KeepArgs order, KeepArgs kg, int E);
 __global__ void dispatch_scatter_kernel(const int32_t* idx, const int32_t* keep,
                                         const int32_t* counts, const int32_t* blockbase, int T,

@@ -643,7 +643,7 @@ __global__ void set_plan_kernel(int32_t* __restrict__ keep, int32_t* __restrict_
                                 KeepArgs order, KeepArgs kg, int E) {
     const int e = threadIdx.x;
     if (e < E) {
-        keep[e] = k.v[e];
+        if (keep) keep[e] = k.v[e];
         plan[e] = order.v[e];
         plan[E + e] = kg.v[e];
     }

@@ -64,9 +64,6 @@ hipError_t launch_act_dgrad(const ActDgradParams& p, long long tiles, hipStream_
 // zeros in each segment's padding rows -- and no mask gradient (dmp unused).
 hipError_t launch_sal_dgrad(const ActDgradParams& p, long long tiles, hipStream_t s);
 hipError_t launch_act_dx(const ActDxParams& p, long long tiles, hipStream_t s);
-// seg[s].kg = seg[s].kk: the down GEMM of the training forward reduces over
-// the kept channels only (the gate/up GEMM computed all of them)
-hipError_t launch_seg_use_kept(SegMeta* seg, int nseg, hipStream_t s);
 // dO = bf16(w_a dY_t) for the *nrouted dispatched rows, dYs = bf16(dY)
 hipError_t launch_train_prep(const float* dy, const int32_t* perm, const float* wts, const int32_t* nrouted,
                              int A, int T, int d, int k, bf16_t* dO, bf16_t* dYs, hipStream_t s);

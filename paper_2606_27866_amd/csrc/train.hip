@@ -39,11 +39,6 @@ __global__ void sample_actions_kernel(ActionWidths aw, const float* __restrict__
     if (action) action[e] = best;
 }
 
-__global__ void seg_use_kept_kernel(SegMeta* seg, int nseg) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < nseg) seg[s].kg = seg[s].kk;
-}
-
 // Rows r < A: dO[r] = bf16(w_a dY_t) with a = perm[r]; rows A + t: dYs[t] =
 // bf16(dY_t).  Eight columns per thread.
 __global__ __launch_bounds__(256) void train_prep_kernel(const float* __restrict__ dy,
@@ -279,11 +274,6 @@ __global__ void action_stats_kernel(const float* __restrict__ per_expert, int E,
 hipError_t launch_sample_actions(const ActionWidths& aw, const float* alpha, const float* gumbel, int E,
                                  int32_t* keep, int32_t* action, hipStream_t s) {
     sample_actions_kernel<<<ceil_div(E, 256), 256, 0, s>>>(aw, alpha, gumbel, E, keep, action);
-    return hipGetLastError();
-}
-
-hipError_t launch_seg_use_kept(SegMeta* seg, int nseg, hipStream_t s) {
-    seg_use_kept_kernel<<<ceil_div(nseg, 256), 256, 0, s>>>(seg, nseg);
     return hipGetLastError();
 }
 
