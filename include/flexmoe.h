@@ -25,7 +25,8 @@
  *     queued on it is ordered after the call's work; no call synchronises the
  *     host.  A forward of a layer with a shared expert may run that expert's
  *     two GEMMs on a second stream of the same device (forked from `stream` by
- *     an event before routing, joined by an event before the combine): it does
+ *     an event before or after the routing kernel, joined by an event before
+ *     the combine): it does
  *     so for T <= 64 and while the shared expert's gate/up GEMM has fewer than
  *     1024 tiles (the training forwards and flexmoe_layer_forward_noalloc
  *     never do).  That stream, its two events and a mutex guarding the fork

@@ -166,10 +166,10 @@ __device__ __forceinline__ int find_segment(const int32_t* tstart, int nseg, int
 // Fragment-blocked layout of a [rows][C] bf16 matrix (C a multiple of 8):
 // 32-row x 8-column blocks of 512 bytes, block (r/32, c/8) at element
 // ((r/32) * (C/8) + c/8) * 256, and inside it element
-// (((c/4) % 2) * 32 + r % 32) * 4 + c % 4 -- the order in which a wave's 64
-// lanes hold runs of 4 consecutive columns of 32 rows (lane -> row lane % 32,
-// columns 4 * (lane / 32) ..), so that the wave's 8-byte accesses cover 512
-// contiguous bytes.  R rows take ceil(R/32) * 32 * C elements.
+// (((c/4) % 2) * 32 + r % 32) * 4 + c % 4: a run of 4 consecutive columns is
+// 8 bytes and the same run of the next row follows it, so a wave's 8-byte
+// accesses cover whole 128-byte lines (16x16 accumulators: lane -> row
+// lane % 16, columns 4 * (lane / 16) ..; four 128-byte pieces per access).  R rows take ceil(R/32) * 32 * C elements.
 __host__ __device__ __forceinline__ size_t frag_blocked(size_t r, int c, int C) {
     return (((r >> 5) * (size_t)(C >> 3) + (size_t)(c >> 3)) << 8) + (size_t)((((c >> 2) & 1) << 5) + (r & 31)) * 4 +
            (c & 3);

@@ -5,8 +5,8 @@
 //   -> combine
 //
 // Launches go to the caller's stream, except the shared expert's two GEMMs,
-// which run on a side stream forked before routing and joined before the
-// combine.  The host never reads routing results back: tile counts live on
+// which may run on a side stream forked before routing (after the routing
+// kernel with the large tiles) and joined before the combine.  The host never reads routing results back: tile counts live on
 // the device and the routed GEMM grids are sized by an upper bound computed
 // from (T, E, I); surplus workgroups exit at once.
 #include <stdarg.h>
@@ -230,7 +230,8 @@ struct KernelTimer {
 // ---- the side stream of the shared expert -------------------------------
 // The shared expert's GEMMs need no routing, so they run on a second stream
 // of the same device, forked from the caller's stream before routing starts
-// and joined before the combine.  Its tiles then fill the compute units the
+// (with the 256 x 256 tiles: after the routing kernel) and joined before the
+// combine.  Its tiles then fill the compute units the
 // routed GEMMs leave idle (their tails, the routing kernels).  One stream
 // and two events per device are created on first use (default priority,
 // non-blocking) and kept for the life of the process; the mutex keeps the
@@ -673,13 +674,11 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
         return FLEXMOE_OK;
     };
 
-    // The shared expert's chain runs on the side stream, forked before the
-    // routing (it needs none); the routed chain follows the routing on the
-    // caller's stream; the combine waits for both.  This pays where the tails
-    // of the GEMMs and
-    // the routing kernels leave compute units idle: decode-sized batches and
-    // shared experts whose gate/up GEMM alone fills fewer than kSideWaves
-    // waves of tiles.  Past that, one launch over all segments keeps each
+    // The shared expert's chain runs on the side stream; the routed chain
+    // follows the routing on the caller's stream; the combine waits for both.
+    // This pays where the tails of the GEMMs and the routing kernels leave
+    // compute units idle: decode-sized batches and shared experts whose
+    // gate/up GEMM alone fills fewer than kSideWaves waves of tiles.  Past that, one launch over all segments keeps each
     // XCD's L2 serving one GEMM at a time.
     // The training forwards compute every routed channel (the routed GEMMs
     // alone fill the chip): one launch over all segments there (measured 2 %

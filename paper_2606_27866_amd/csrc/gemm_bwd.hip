@@ -18,12 +18,14 @@
 // On the Qwen1.5-MoE shape with 4096 tokens the loop took, against the one
 // before it (both waves of a SIMD on the same step, 32x32x16 MFMAs): wgrad
 // 568 -> 560,
-// saliency dgrad 238 -> 220, training dgrad 358 -> 318, dx 349 -> 320 us.
+// saliency dgrad 238 -> 220, training dgrad 358 -> 318, dx 349 -> 320 us.  With
+// segments on cache lines (below) wgrad takes 454 and the saliency dgrad 204.
 //   dgrad: A = dO [A][d] (a segment's rows), B = W_down^T [E][I][d] (a
 //          transposed copy of the down weights), K = d.
 //   wgrad: A = x^T or dO^T [d][ldt], B = dG^T, dU^T or h^T [I][ldt], with a
 //          segment's rows as K (columns prow0 .. prow0 + rows of the
-//          transposed copies, zero-padded to a multiple of 8).
+//          transposed copies, zero-padded to a multiple of 8; segments start
+//          on multiples of TileShape::pad columns).
 #include "mfma_pingpong.h"
 #include "saliency.h"
 #include "train.h"
@@ -215,8 +217,8 @@ __device__ __forceinline__ bool train_tile(const SegMeta* seg, int hs, int nseg,
 
 // dgrad + SwiGLU backward; tile = 256 rows x 256 channels.  The B fragment
 // goes first: lane -> row, registers -> runs of 4 channels.  g and u are read
-// in their fragment-blocked layout (a wave's 8-byte reads cover 512
-// contiguous bytes); dG and dU are staged through LDS, half of the tile's
+// in their fragment-blocked layout (a wave's 8-byte reads cover whole
+// 128-byte lines); dG and dU are staged through LDS, half of the tile's
 // channels at a time, and stored as whole 16-byte pieces.
 //   kMode 2 (masked layer's training backward): shared expert included, the
 //     mask gradient's partial sums, dG/dU row-major [rows][C] over the kept

@@ -1,7 +1,7 @@
 // Building blocks of the bf16 MFMA GEMM kernels (gfx950): operands are
 // staged in LDS as K tiles of 64 bf16 per row (128-byte rows), loaded straight
 // from global memory by buffer_load ... lds, and read back as
-// v_mfma_f32_32x32x16_bf16 fragments.
+// v_mfma_f32_16x16x32_bf16 fragments.
 #pragma once
 
 #include "kernels.h"
@@ -12,7 +12,6 @@ namespace mfma {
 constexpr int BK = 64;               // K elements per LDS row (one K tile)
 constexpr int ROWB = BK * 2;         // bytes per LDS row
 constexpr int CHUNKS = ROWB / 16;    // 16-byte chunks per LDS row
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_ptr_t;
 
 // 16 lanes of a fragment read hit 16 consecutive rows at one logical chunk;
@@ -53,19 +52,6 @@ __device__ __forceinline__ void barrier_no_fence() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// Scheduling template for one 16-deep step: NMF MFMAs, NV vector memory
-// reads (DMA) and NRD LDS reads, issued round-robin.
-template <int NMF, int NV, int NRD>
-__device__ __forceinline__ void sched_interleave() {
-    constexpr int R = NMF > NRD ? (NMF > NV ? NMF : NV) : (NRD > NV ? NRD : NV);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (r < NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        if (r < NV) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // VMEM read (DMA)
-        if (r < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-    }
 }
 
 }  // namespace mfma

@@ -62,8 +62,8 @@ __global__ __launch_bounds__(TTHREADS) void transpose_batched_kernel(const bf16_
     }
 }
 
-// Padded rows q0 .. q0+63 (every routed segment takes packed_width(rows)
-// rows from its prow0) x columns n0 .. n0+63 of x (blockIdx.z = 0) or of
+// Padded rows q0 .. q0+63 (every routed segment takes its rows rounded
+// up to TileShape::pad from its prow0) x columns n0 .. n0+63 of x (blockIdx.z = 0) or of
 // dO = w_a dY_t (blockIdx.z = 1), written transposed; padding rows are zeros.
 __global__ __launch_bounds__(TTHREADS) void sal_prep_kernel(SalPrepParams p) {
     __shared__ bf16_t tile[TT][TPAD];
