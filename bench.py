@@ -395,7 +395,8 @@ class Workload:
 
 def gate_up_kernel_name(cfg, T):
     """The kernel the library runs for the gate/up GEMM at T tokens (its own
-    thresholds, kernels.h)."""
+    thresholds, kernels.h).  Between decode and prefill, where the routed
+    experts may take gemm1_mid_kernel, no workload here is timed."""
     if cfg.dtype != 1:
         return "gemm1_f32_kernel"
     if T > DECODE_MAX_T:

@@ -233,11 +233,11 @@ __device__ __forceinline__ void f32_tile(const Gemm1Params<float>& p1, const Gem
     }
 }
 
-__global__ __launch_bounds__(FTHREADS, 2) void gemm1_f32_mfma_kernel(Gemm1Params<float> p) {
+__global__ __launch_bounds__(FTHREADS, 2) void gemm1_f32_kernel(Gemm1Params<float> p) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[F32_SMEM];
     f32_tile<true>(p, Gemm2Params<float>{}, smem);
 }
-__global__ __launch_bounds__(FTHREADS, 2) void gemm2_f32_mfma_kernel(Gemm2Params<float> p) {
+__global__ __launch_bounds__(FTHREADS, 2) void gemm2_f32_kernel(Gemm2Params<float> p) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[F32_SMEM];
     f32_tile<false>(Gemm1Params<float>{}, p, smem);
 }
@@ -248,7 +248,7 @@ namespace {
 constexpr int BM = kF32BM, BN = kF32BN, BK = 16;
 }
 
-__global__ __launch_bounds__(256) void gemm1_f32_kernel(Gemm1Params<float> p) {
+__global__ __launch_bounds__(256) void gemm1_f32_valu_kernel(Gemm1Params<float> p) {
     __shared__ float As[BK][BM + 4];
     __shared__ float Bg[BK][BN + 4];
     __shared__ float Bu[BK][BN + 4];
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(256) void gemm1_f32_kernel(Gemm1Params<float> p) {
         }
 }
 
-__global__ __launch_bounds__(256) void gemm2_f32_kernel(Gemm2Params<float> p) {
+__global__ __launch_bounds__(256) void gemm2_f32_valu_kernel(Gemm2Params<float> p) {
     __shared__ float As[BK][BM + 4];
     __shared__ float Bs[BK][BN + 4];
     int s, local;
@@ -390,15 +390,15 @@ __global__ __launch_bounds__(256) void gemm2_f32_kernel(Gemm2Params<float> p) {
 
 hipError_t launch_gemm1_f32(const Gemm1Params<float>& p, int grid, hipStream_t s, bool matrix) {
     if (grid <= 0) return hipSuccess;
-    if (matrix) gemm1_f32_mfma_kernel<<<grid, FTHREADS, 0, s>>>(p);
-    else gemm1_f32_kernel<<<grid, 256, 0, s>>>(p);
+    if (matrix) gemm1_f32_kernel<<<grid, FTHREADS, 0, s>>>(p);
+    else gemm1_f32_valu_kernel<<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm2_f32(const Gemm2Params<float>& p, int grid, hipStream_t s, bool matrix) {
     if (grid <= 0) return hipSuccess;
-    if (matrix) gemm2_f32_mfma_kernel<<<grid, FTHREADS, 0, s>>>(p);
-    else gemm2_f32_kernel<<<grid, 256, 0, s>>>(p);
+    if (matrix) gemm2_f32_kernel<<<grid, FTHREADS, 0, s>>>(p);
+    else gemm2_f32_valu_kernel<<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
