@@ -72,12 +72,13 @@ __device__ __forceinline__ void rank_keys(const RouteScratch& rs, const uint32_t
 // The ranks of NT tokens at once.  kOnce: larger keys are counted with one
 // compare per pair; every pair of different keys adds one to the sum of all ranks, so
 // a sum below E (E - 1) / 2 tells that some keys are equal, and only then the
-// token is ranked again with the ids breaking ties.  Up to 16 experts the sum
-// costs more than the second compares (8 experts: 0.4 us of a 26 us forward).
+// token is ranked again with the ids breaking ties.  Up to kRankTwiceExperts the
+// sum costs more than the second compares (8 experts: 0.4 us of a 26 us forward).
+constexpr int kRankTwiceExperts = 16;
 template <int NT, int NQ, bool kOnce>
 __device__ __forceinline__ void rank_tokens(const RouteScratch (&rs)[NT], const uint32_t (&mk)[NT][4], int E, int E8,
                                             int lane, int (&rank)[NT][4]) {
-    if (!kOnce || E <= 16) {
+    if (!kOnce || E <= kRankTwiceExperts) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) rank_keys<NQ>(rs[t], mk[t], E8, lane, rank[t]);
         return;
@@ -485,11 +486,8 @@ __global__ __launch_bounds__(64) void dispatch_scatter_kernel(
 // tokens were routed by route_kernel (spread over several compute units):
 // the waves read their tokens' expert ids instead.
 // kPairs: the waves route their tokens two at a time and rank them with one
-// compare per pair of experts (more than one token per wave).  Steps of at
-// most 16 tokens keep a kernel without either: the pairs' code and LDS cost a
-// small layer 0.5 us there, and routing a Qwen2-57B-shaped single token 2 us
-// sooner made its step 2 us longer (121 -> 124): the routed gate/up GEMM then
-// contends with the shared expert's, whose chain ends last.
+// compare per pair of experts (launch_dispatch_small: more than one token per
+// wave and more than kRankTwiceExperts experts), else one after another.
 template <bool kPairs>
 __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
     const float* __restrict__ logits, int T, int E, int k, int norm_topk,
@@ -536,9 +534,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
                 atomicAdd(&hist[wave][id], 1);  // a count: arrival order does not matter
             }
         };
-        // two tokens at a time (T = 37 and 64, 60 experts: this kernel 17.9 ->
-        // 15.0 and 23.9 -> 17.9 us between events); the next pair's logits are
-        // loaded while this one is ranked
+        // the next tokens' logits are loaded while these are ranked
         constexpr int NT = kPairs ? 2 : 1;
         float vn[NT][4];
         auto load_next = [&](int t) {
@@ -561,11 +557,12 @@ __global__ __launch_bounds__(64 * kSmallWaves) void dispatch_small_kernel(
                 keep_token(t, id[0], w[0]);
                 keep_token(t + 1, id[1], w[1]);
             }
-        if (t < t1) {
+        for (; t < t1; ++t) {  // with pairs: the odd one left
             int id[1];
             float w[1], v[1][4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[0][q] = vn[0][q];
+            if (!kPairs && t + 1 < t1) load_next(t + 1);
             route_tokens<1, kPairs>(v, E, k, norm_topk, lane, reinterpret_cast<RouteScratch(&)[1]>(rs[wave]), id, w);
             keep_token(t, id[0], w[0]);
         }
@@ -623,7 +620,17 @@ hipError_t launch_dispatch_small(const float* logits, int T, int E, int k, int n
                                  int pre_routed, int32_t* idx, float* wts, int32_t* counts, int32_t* perm,
                                  int32_t* pos, int32_t* offsets, SegMeta* seg, int32_t* t1start, int32_t* t2start,
                                  int32_t* order2, hipStream_t s) {
-    if (T <= kSmallWaves || pre_routed)
+    // Pairs of tokens pay where a wave has several of them and ranking is long
+    // (no-allocation forward, one at a time -> pairs: Qwen1.5-MoE shape, 60
+    // experts, at 17, 37 and 64 tokens 109.0 -> 106.8, 146.1 -> 142.3 and 169.3
+    // -> 162.7 us; 24 experts at 24 and 64 tokens 28.8 -> 28.2 and 38.6 -> 36.2;
+    // 256 experts at 64 tokens 235 -> 135).  Up to 16 experts they cost more
+    // code and LDS than they save (8 and 16 experts at 20 to 64 tokens 24.3 ->
+    // 24.6, 28.2 -> 29.0, 35.3 -> 35.9 us).  With one token per wave they cost a
+    // small layer 0.5 us, and routing a Qwen2-57B-shaped single token 2 us
+    // sooner made its step 2 us longer (121 -> 124): the routed gate/up GEMM
+    // then contends with the shared expert's, whose chain ends last.
+    if (T <= kSmallWaves || E <= kRankTwiceExperts || pre_routed)
         dispatch_small_kernel<false><<<1, 64 * kSmallWaves, 0, s>>>(logits, T, E, k, norm_topk, keep, I, I_shared, d, ts,
                                                                     packed_limit, plan, pre_routed, idx, wts, counts,
                                                                     perm, pos, offsets, seg, t1start, t2start, order2);
