@@ -552,7 +552,8 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // -> small: Qwen2-57B shape at 80 and 230 tokens 489 -> 444 and 536 -> 529
     // us, Qwen1.5-MoE shape at 100, 300 and 1000 155 -> 134, 171 -> 163 and
     // 252 -> 246).
-    const bool mid = bf16 && !decode && !train && sh_few && mid_tiles(T, D.top_k, D.E, D.I, kComputeUnits);
+    const bool mid = bf16 && !decode && !train && sh_few &&
+                     mid_tiles(T, D.top_k, D.E, D.I, D.d, has_shared, kComputeUnits);
     const int ks2 = train ? 0 : shared_ks2(D, T);
     const int parts = train ? (has_shared ? 1 : 0) : shared_parts(D, T);
     if (train == 2) {

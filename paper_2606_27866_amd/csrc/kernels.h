@@ -180,12 +180,29 @@ constexpr int kSharedSplit2T = 16;  // above this many (decode) tokens the share
 //     fewer than kMidWaves per compute unit, so that their last wave is a large
 //     part of the launch (Qwen1.5-MoE shape, n = 68 / 100: 215 / 266 us against
 //     242 / 308; Mixtral shape, n = 100: 437 against 512; past that, n = 137
-//     and 150, the two are equal).
-constexpr int kMidRows = 48, kMidRowsFew = 128, kMidWaves = 4;
-inline bool mid_tiles(int T, int top_k, int E, int I, int compute_units) {
-    const long long A = (long long)T * top_k;
+//     and 150, the two are equal);
+//   but no more than kMidRowsFull where the large tiles of the full width have
+//     no such wave: without a shared expert, whose tiles fill it too, and with
+//     both GEMMs' tiles filling 7/8 of their waves, each weighted with its
+//     reduction, and reductions of kMidFullK on average, beside which a tile's
+//     prologue and epilogue are short.  At n = 125 and all channels, small
+//     against large: 8 experts of 8192 channels, hidden size 8192, 691 / 584 us;
+//     16 of 4096, 4096, 363 / 333; 64 of 1536, 4096, 554 / 513; 24 of 2560, 5120,
+//     467 / 404; 32 of 2048, 3072, 297 / 292 (at 60 % 474 / 476, 292 / 305 (70 %),
+//     408 / 401, 340 / 345, 221 / 234).  Where one of the three does not hold:
+//     waves 3/4 full, 16 of 3072, 3072, 238 / 237 (n = 102: 220 / 227); short
+//     reductions, 32 of 2048, 2048, 211 / 233; the 16 of 4096 beside a shared
+//     expert of 4096 channels, 443 / 449.  At n = 75 to 87 the small tiles are at
+//     worst 2 % behind (8 of 8192 at n = 75: 516 / 555).
+constexpr int kMidRows = 48, kMidRowsFew = 128, kMidWaves = 4, kMidRowsFull = 96, kMidFullK = 2304;
+inline bool mid_tiles(int T, int top_k, int E, int I, int d, bool has_shared, int compute_units) {
+    const long long A = (long long)T * top_k, cu = compute_units;
     if (A <= (long long)kMidRows * E) return true;
-    return A <= (long long)kMidRowsFew * E && (long long)E * ceil_div(I, kBigBN1) < (long long)kMidWaves * compute_units;
+    const long long n1 = (long long)E * ceil_div(I, kBigBN1), n2 = (long long)E * ceil_div(d, kBigBN2);
+    if (A > (long long)kMidRowsFew * E || n1 >= kMidWaves * cu) return false;
+    if (A <= (long long)kMidRowsFull * E || has_shared) return true;
+    const long long waves1 = (n1 + cu - 1) / cu, waves2 = (n2 + cu - 1) / cu, k = waves1 * d + waves2 * I;
+    return 8 * (n1 * d + n2 * I) < 7 * k * cu || k < kMidFullK * (waves1 + waves2);
 }
 
 __global__ void route_kernel(const float* logits, int T, int E, int k, int norm_topk, int32_t* idx,

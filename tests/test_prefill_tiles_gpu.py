@@ -105,3 +105,33 @@ def test_backward_segment_and_reduction_edges(d, I, I_s):
     sal.add_batch(xd, ld, fm.to_device(tgt))
     torch.cuda.synchronize()
     check_scores(sal.scores.cpu().numpy(), oracle.channel_saliency([(x, lg, tgt)], *w, 1, 0, *s))
+
+
+@pytest.mark.parametrize("T", [1536, 1537, 2048, 2049])
+def test_tile_rule_edges(T):
+    """A layer whose large tiles fill their waves, without a shared expert: 96
+    rows per expert are the last that take the small tiles (elsewhere 128)."""
+    import torch
+    d, E, I = 3072, 16, 2048
+    say("tile rule T", T)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+
+    def rnd(*shape, std):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+
+    w = [rnd(E, I, d, std=0.02), rnd(E, I, d, std=0.02), rnd(E, d, I, std=0.02)]
+    x, lg = rnd(T, d, std=1.0), torch.randn((T, E), device="cuda", generator=gen)
+    keep = np.array([I, 0, 1, 127, 128, 129, 1000, I - 1] * 2, np.int32)
+    layer = fm.Layer(d, E, I, 1, 0, synth.BF16, 0, max_tokens=T)
+    layer.set_weights(*w)
+    layer.set_budget(keep)
+    y = layer.forward(x, lg).float()
+    p = torch.softmax(lg, 1)
+    ref = torch.zeros((T, d), device="cuda")
+    for e in range(E):
+        n, t = int(keep[e]), torch.nonzero(lg.argmax(1) == e).squeeze(1)
+        xe = x[t].float()
+        h = torch.nn.functional.silu(xe @ w[0][e, :n].float().T) * (xe @ w[1][e, :n].float().T)
+        ref[t] = p[t, e].unsqueeze(1) * (h @ w[2][e, :, :n].float().T)
+    check_y(y.cpu().numpy(), ref.cpu().numpy(), BF16_TOL)
