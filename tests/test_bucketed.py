@@ -4,6 +4,9 @@ extra activations are zeroed.  Its results must be those of the masked layer
 (the padded channels contribute exact zeros), so on the GPU it is checked
 against the ragged forward (same bits) and the oracle.
 """
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -31,7 +34,25 @@ CASES = [
     ("b_decode", 8, 256, 16, 200, 4, 128, synth.BF16, 0),
     # 17..64 tokens: 64-wide weight-streaming tiles
     ("b_decode48", 48, 264, 12, 200, 4, 136, synth.BF16, 1),
+    # 175 rows per expert: 256 x 256 tiles (the prefill cases above take the 128 x 128 ones)
+    ("b_large", 700, 256, 8, 320, 2, 0, synth.BF16, 1),
+    ("b_large_shared", 700, 136, 8, 264, 2, 256, synth.BF16, 0),
 ]
+
+
+def test_large_cases_are_past_the_small_tiles():
+    """The cases named large, here and in the other tests of a whole forward,
+    have more rows per expert than the 128 x 128 tiles ever take."""
+    from tests import test_clipped, test_graph_replay, test_zz_no_alloc
+    src = open(os.path.join(os.path.dirname(fm.__file__), "csrc", "kernels.h")).read()
+    limit = int(re.search(r"kMidRowsFew = (\d+)", src).group(1))
+    cases = [(c[0], c[1], c[3], c[5]) for m in (test_clipped, test_graph_replay) for c in m.CASES]
+    cases += [(c[0], c[1], c[3], c[5]) for c in CASES]
+    cases += [(c[0], T, c[2], c[4]) for c in test_zz_no_alloc.CASES for T in c[8]]
+    large = [(T, E, k) for name, T, E, k in cases if "large" in name]
+    assert len(large) == 7
+    assert all(T * k > limit * E for T, E, k in large)
+    assert test_clipped.WRONG_TABLE_T[-1] * 2 > limit * 8
 
 
 def case_keeps(E, I, seed):

@@ -125,7 +125,12 @@ CASES = [
     ("c_prefill_shared", 200, 512, 16, 192, 4, 256, synth.BF16, 0),
     ("c_decode", 8, 256, 16, 200, 4, 128, synth.BF16, 0),
     ("c_decode64", 64, 128, 24, 72, 8, 64, synth.BF16, 1),
+    # 175 rows per expert: 256 x 256 tiles (the prefill cases above take the 128 x 128 ones)
+    ("c_large", 700, 256, 8, 320, 2, 0, synth.BF16, 1),
+    ("c_large_shared", 700, 136, 8, 264, 2, 256, synth.BF16, 0),
 ]
+# 2 of 8 experts per token: weight-streaming, 128 x 128 and 256 x 256 tiles
+WRONG_TABLE_T = [40, 300, 700]
 
 
 def case_keeps(E, I, seed):
@@ -179,7 +184,7 @@ def test_gpu_clipped_matches_online_and_oracle(spec):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("T", [40, 300])
+@pytest.mark.parametrize("T", WRONG_TABLE_T)
 def test_gpu_clipped_wrong_table_stays_inside_the_buffers(T):
     """keep_dev wider than the exported budget: experts whose packed block
     would end past packed_channels are skipped, the others read the packed

@@ -12,10 +12,12 @@ from paper_2606_27866_amd import synth
 from tests.gpu_util import mini_layer, say
 
 CASES = [
-    # name, T, d, E, I, k, I_s  (T <= 64: decode kernels; larger: prefill tiles)
+    # name, T, d, E, I, k, I_s  (T <= 64: decode kernels; 75 rows per expert: 128 x 128
+    # tiles; 175: 256 x 256 tiles, with the side stream forked after the routing)
     ("g_decode", 8, 256, 16, 192, 4, 128),
     ("g_decode1", 1, 256, 16, 192, 4, 128),
     ("g_prefill", 300, 256, 8, 320, 2, 256),
+    ("g_large", 700, 256, 8, 320, 2, 256),
 ]
 
 

@@ -9,7 +9,7 @@ for bit against the workspace forward's, y within the bar of the dtype
 and y against the oracle at the same bar.  Decode-sized batches cover the
 16- and 64-wide weight-streaming tiles with the shared expert's split down
 reduction in the same launches as the routed experts; larger batches the
-prefill tiles.
+128 x 128 tiles, and with more rows per expert the 256 x 256 ones.
 """
 import numpy as np
 import pytest
@@ -26,6 +26,7 @@ CASES = [
     ("prefill_shared", 512, 60, 192, 4, 256, 0, synth.BF16, (200, 70)),
     ("no_shared", 256, 8, 320, 2, 0, 1, synth.BF16, (300, 3)),
     ("fp32", 256, 8, 512, 2, 64, 1, synth.F32, (64, 9)),
+    ("large_shared", 256, 8, 192, 2, 256, 0, synth.BF16, (700, 520)),
 ]
 
 
