@@ -26,7 +26,10 @@ def special_scores(E, I, seed):
 @pytest.mark.parametrize("dtype,E,I,d,offset", [
     (synth.BF16, 3, 8, 8, 0), (synth.BF16, 2, 256, 24, 0), (synth.BF16, 2, 264, 72, 0), (synth.BF16, 2, 2048, 16, 0),
     (synth.BF16, 2, 2056, 40, 0), (synth.BF16, 2, 4360, 24, 0), (synth.BF16, 1, 32776, 8, 0),
-    (synth.BF16, 2, 264, 72, 1), (synth.F32, 2, 520, 24, 0), (synth.F32, 1, 16392, 8, 0), (synth.F32, 2, 264, 72, 1)])
+    (synth.BF16, 2, 264, 72, 1), (synth.F32, 2, 520, 24, 0), (synth.F32, 1, 16392, 8, 0), (synth.F32, 2, 264, 72, 1),
+    # rows of W_down per workgroup: 5 and 3 with a remainder, one, and one that fills 64 KB of LDS
+    (synth.BF16, 2, 2400, 24, 0), (synth.BF16, 2, 3800, 16, 0), (synth.BF16, 2, 14336, 24, 0),
+    (synth.BF16, 1, 32768, 8, 0), (synth.F32, 2, 7168, 24, 0), (synth.F32, 1, 16384, 8, 0)])
 def test_rank_reorder_edges(dtype, E, I, d, offset):
     import torch
     say("reorder dtype", dtype, "E", E, "I", I, "d", d, "offset", offset)
