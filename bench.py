@@ -10,7 +10,8 @@ Inputs are seeded synthetic tensors already resident in HBM; the weights are
 rotated over --copies device copies so that no step finds them in the 256 MB
 last-level cache.
 
-Prints ONE JSON line on stdout.  The headline (`value`, `ms_per_step`) is the
+Prints ONE JSON line on stdout, short enough for a log's tail (--detail FILE
+writes every figure).  The headline (`value`, `ms_per_step`) is the
 Mixtral-8x7B-shaped layer (T = 16384, d = 4096, 8 experts of I = 14336, top-2,
 Zipf(1.2) expert load, its own 50 % keep table): tokens/s over exactly K
 timed steps, after at least W warm-up steps and --min-warmup-s seconds.
@@ -100,6 +101,7 @@ def parse(argv=None):
                     help="skip timing the vendor library's dense bf16 GEMM (torch.matmul) on two reference shapes")
     ap.add_argument("--dense-reference-only", action="store_true",
                     help="only time the dense reference GEMMs (for a counter run of the vendor kernel)")
+    ap.add_argument("--detail", default="", help="also write every figure, unrounded, to this JSON file")
     ap.add_argument("--copy-calibration-mib", type=int, default=0,
                     help="after timing, copy this many MiB device-to-device once, so that a "
                          "counter run sees a plain copy of known size (HBM byte calibration)")
@@ -119,6 +121,45 @@ def no_gc():
     finally:
         if was:
             gc.enable()
+
+
+# The stdout line is read back from the tail of a log: it stays below LINE_MAX
+# characters.  Numbers go out with five significant digits; while the line is
+# too long, the keys of LINE_DROP leave the sections one after another (they
+# stand in the --detail file), then whole sections, the largest first.
+LINE_MAX = 14000
+LINE_KEEP = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+             "vs_baseline", "dtype", "data", "config", "step_ms", "roofline", "layer")
+LINE_DROP = ("timing", "note", "loss", "w_down_t", "upstream_gradient", "builds", "kernels_ms", "n", "mean",
+             "warmup_steps", "ms_per_step_instrumented", "summed_launch_ms_per_step", "launches_per_step",
+             "concurrent_launches", "flops_per_step", "bytes_per_step", "flops_per_launch", "bytes_per_launch",
+             "theta_bytes_per_launch", "p10", "p90", "switch_cost", "fixed", "pointer_switch")
+
+
+def result_line(out):
+    """The JSON line of a run, at most LINE_MAX characters."""
+    def slim(v, drop):
+        if isinstance(v, dict):
+            return {k: slim(x, drop) for k, x in v.items() if k not in drop}
+        if isinstance(v, (list, tuple)):
+            return [slim(x, drop) for x in v]
+        return float("%.5g" % v) if isinstance(v, float) else v
+
+    def line(drop):
+        return json.dumps({k: v if k in ("value", "ms_per_step") else slim(v, () if k in LINE_KEEP else drop)
+                           for k, v in out.items()})
+
+    out = dict(out)
+    for n in range(len(LINE_DROP) + 1):
+        text = line(LINE_DROP[:n])
+        if len(text) <= LINE_MAX:
+            return text
+    for k in sorted((k for k in out if k not in LINE_KEEP), key=lambda k: -len(json.dumps(slim(out[k], LINE_DROP)))):
+        del out[k]
+        text = line(LINE_DROP)
+        if len(text) <= LINE_MAX:
+            break
+    return text
 
 
 def kernel_src_hash(read=None):
@@ -1050,7 +1091,10 @@ def main(argv=None):
     if dense is not None:
         out["dense_gemm_reference"] = dense
     out["wall_s"] = time.time() - t_start
-    print(json.dumps(out), flush=True)
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(out, f, indent=1)
+    print(result_line(out), flush=True)
 
 
 if __name__ == "__main__":

@@ -193,3 +193,33 @@ def test_cpu_info_names_the_model_and_counts():
     info = bench.cpu_info()
     assert info["nproc"] >= 1 and 1 <= info["usable_cpus"] <= info["nproc"]
     assert isinstance(info["cpu_model"], str) and info["cpu_model"]
+
+
+def _nested(depth, width):
+    v = {"note": "x" * 80, "kernels_ms": {"k%d" % i: i / 3.0 for i in range(8)}, "tokens_per_s": 1e6 / 3.0}
+    return v if depth == 0 else dict(v, rows=[_nested(depth - 1, width) for _ in range(width)])
+
+
+@pytest.mark.parametrize("width", [1, 8, 40])
+def test_result_line_fits_a_log_tail(width):
+    """Short sections go out whole; long ones first lose their least needed
+    keys, then go themselves; what the line must hold is never cut."""
+    out = {k: 1 for k in bench.LINE_KEEP}
+    out.update(value=4556185.242005823, ms_per_step=3.595990753173828, config={"note": "n", "T": 16384},
+               roofline={"achieved": 1379.6897771094511, "kernels_ms": {"a": 0.5}}, first=_nested(2, width),
+               second=_nested(1, width), small={"ms": 2.0 / 3.0})
+    text = bench.result_line(out)
+    assert len(text) <= bench.LINE_MAX < 16000 and "\n" not in text
+    line = json.loads(text)
+    assert set(bench.LINE_KEEP) <= set(line)
+    assert line["value"] == out["value"] and line["ms_per_step"] == out["ms_per_step"]
+    assert line["config"] == out["config"]
+    assert line["roofline"] == {"achieved": 1379.7, "kernels_ms": {"a": 0.5}}
+    assert line["small"] == {"ms": 0.66667} and line["second"]["tokens_per_s"] == 333330.0
+    if width == 1:
+        assert line["first"]["note"] and line["first"]["rows"][0]["rows"][0]["kernels_ms"]["k1"] == 0.33333
+    elif width == 8:
+        assert "note" not in line["first"] and line["first"]["rows"][7]["rows"][7]["tokens_per_s"] == 333330.0
+    else:
+        assert "first" not in line
+    assert out["first"]["note"]  # the result itself stays whole
