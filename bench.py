@@ -52,7 +52,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3      # MI355X fp32 vector
+PEAK_F32_TFLOPS = 157.3      # MI355X fp32 matrix cores
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 RIDGE = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 DECODE_MAX_T = 64            # the library runs its weight-streaming GEMMs for T <= 64 (bf16)

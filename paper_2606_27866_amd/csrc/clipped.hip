@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void export_clipped_kernel(ExportArgs a, const
         const u32x4* w = reinterpret_cast<const u32x4*>((blockIdx.z ? wu_r : wg_r) + src);
         u32x4* out = reinterpret_cast<u32x4*>((blockIdx.z ? wu_c : wg_c) + dst);
         const size_t kept = (size_t)k * d / VEC, n = (size_t)kp * d / VEC;  // d % 8 == 0
-        for (size_t i = first; i < n; i += step) 
+        for (size_t i = first; i < n; i += step)
             __builtin_nontemporal_store(i < kept ? __builtin_nontemporal_load(w + i) : zero, out + i);
     } else {
         // down: packed element (n, c) = ranked (n, c) for c < k, else 0; rows

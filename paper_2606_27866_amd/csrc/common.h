@@ -169,7 +169,8 @@ __device__ __forceinline__ int find_segment(const int32_t* tstart, int nseg, int
 // (((c/4) % 2) * 32 + r % 32) * 4 + c % 4: a run of 4 consecutive columns is
 // 8 bytes and the same run of the next row follows it, so a wave's 8-byte
 // accesses cover whole 128-byte lines (16x16 accumulators: lane -> row
-// lane % 16, columns 4 * (lane / 16) ..; four 128-byte pieces per access).  R rows take ceil(R/32) * 32 * C elements.
+// lane % 16, columns 4 * (lane / 16) ..; four 128-byte pieces per access).
+// R rows take ceil(R/32) * 32 * C elements.
 __host__ __device__ __forceinline__ size_t frag_blocked(size_t r, int c, int C) {
     return (((r >> 5) * (size_t)(C >> 3) + (size_t)(c >> 3)) << 8) + (size_t)((((c >> 2) & 1) << 5) + (r & 31)) * 4 +
            (c & 3);

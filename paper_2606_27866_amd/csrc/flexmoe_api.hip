@@ -6,9 +6,10 @@
 //
 // Launches go to the caller's stream, except the shared expert's two GEMMs,
 // which may run on a side stream forked before routing (after the routing
-// kernel with the large tiles) and joined before the combine.  The host never reads routing results back: tile counts live on
-// the device and the routed GEMM grids are sized by an upper bound computed
-// from (T, E, I); surplus workgroups exit at once.
+// kernel with the large tiles) and joined before the combine.  The host never
+// reads routing results back: tile counts live on the device and the routed
+// GEMM grids are sized by an upper bound computed from (T, E, I); surplus
+// workgroups exit at once.
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -528,8 +529,8 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     const int NB = num_chunks(T);
     const int nseg = D.E + (has_shared ? 1 : 0);
     const bool bf16 = D.dtype == FLEXMOE_BF16;
-    // kernel family: weight streaming for decode-sized T, large MFMA tiles
-    // otherwise (bf16); LDS-tiled FMA for fp32
+    // kernel family (bf16): weight streaming for decode-sized T, MFMA tiles
+    // otherwise; fp32: matrix-core tiles, past their offsets' reach vector-ALU ones
     const bool decode = bf16 && T <= kDecodeMaxT && !train;
     // The shared expert's GEMMs run on the side stream (see below) for
     // decode-sized batches and while its gate/up GEMM has few prefill tiles.
@@ -679,8 +680,9 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // follows the routing on the caller's stream; the combine waits for both.
     // This pays where the tails of the GEMMs and the routing kernels leave
     // compute units idle: decode-sized batches and shared experts whose
-    // gate/up GEMM alone fills fewer than kSideWaves waves of tiles.  Past that, one launch over all segments keeps each
-    // XCD's L2 serving one GEMM at a time.
+    // gate/up GEMM alone fills fewer than kSideWaves waves of tiles.  Past
+    // that, one launch over all segments keeps each XCD's L2 serving one GEMM
+    // at a time.
     // The training forwards compute every routed channel (the routed GEMMs
     // alone fill the chip): one launch over all segments there (measured 2 %
     // faster than the split on the Qwen1.5 shape).
@@ -953,8 +955,8 @@ SalLayout sal_layout(const flexmoe_layer_desc& D, int T) { return sal_carve(D, T
 // The layout of a call.  The weight-gradient GEMMs read 128-byte pieces of the
 // transposed copies' rows; segments that start on 64-row boundaries put each
 // in one cache line instead of two (wgrad, Qwen1.5-MoE shape with 4096 and
-// 16384 tokens 508 -> 454 and 1357 -> 1110 us, Mixtral shape with 2048 2815 ->
-// 2288).  With few rows per expert, n = T top_k / E, writing the padding costs
+// 16384 tokens 600 -> 517 and 1690 -> 1328 us, Mixtral shape with 2048 2570 ->
+// 2074).  With few rows per expert, n = T top_k / E, writing the padding costs
 // more than it saves, and it saves more the more channel tiles read a row:
 // 64-row boundaries from n = kSalPadRows and n ceil(I / kSalTile) =
 // kSalPadReads on.  A batch with 8-row against 64-row boundaries: Qwen1.5-MoE

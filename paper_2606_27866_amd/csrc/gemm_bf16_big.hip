@@ -36,7 +36,7 @@
 // expert gets a few hundred tokens).  A tile with R rows runs the variant in
 // which each wave multiplies ceil(R/64) fragments of 16 rows per A half, so
 // MFMA work follows the rows at a 64-row granularity; the loads stay the same
-// (rows past the segment read the zero page).
+// (rows past the segment read zeros).
 #include "mfma_pingpong.h"
 
 namespace flexmoe {
@@ -297,8 +297,8 @@ __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void gemm1_big_kernel(G
     big_tile<true, 0, XG>(p, Gemm2Params<bf16_t>{}, smem);
 }
 
-// The gate/up GEMM of the training forward: the same tiles, plus the
-// transposed g, u and h copies of the routed segments (Gemm1Params).
+// The gate/up GEMM of the channel saliency: the same tiles, plus g and u of
+// the routed rows (fragment-blocked) and their h transposed (Gemm1Params).
 __global__ __launch_bounds__(THREADS, PP_WAVES_PER_SIMD) void gemm1_big_train_kernel(Gemm1Params<bf16_t> p) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[PP_SMEM];
     big_tile<true, 1>(p, Gemm2Params<bf16_t>{}, smem);

@@ -17,9 +17,9 @@
 // its epilogue are 8-byte accesses.
 // On the Qwen1.5-MoE shape with 4096 tokens the loop took, against the one
 // before it (both waves of a SIMD on the same step, 32x32x16 MFMAs): wgrad
-// 568 -> 560,
-// saliency dgrad 238 -> 220, training dgrad 358 -> 318, dx 349 -> 320 us.  With
-// segments on cache lines (below) wgrad takes 454 and the saliency dgrad 204.
+// 603 -> 600, saliency dgrad 254 -> 228, training dgrad 358 -> 319, dx 338 ->
+// 298 us.  With segments on cache lines (below) wgrad takes 517 and the saliency
+// dgrad 223.
 //   dgrad: A = dO [A][d] (a segment's rows), B = W_down^T [E][I][d] (a
 //          transposed copy of the down weights), K = d.
 //   wgrad: A = x^T or dO^T [d][ldt], B = dG^T, dU^T or h^T [I][ldt], with a

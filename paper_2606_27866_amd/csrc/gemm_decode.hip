@@ -214,7 +214,7 @@ __device__ __forceinline__ void wide_tile(const Gemm1Params<bf16_t>& p1, const G
             barrier_no_fence();
             // unconditional, so that the compiler's count of outstanding
             // loads stays exact: past the last batch every copy is masked
-            // and reads the zero page
+            // and reads zeros
             issue(b + 2);
             compute(b);
         }

@@ -11,10 +11,10 @@
 // K of one row and feeds four MFMAs: MFMA q multiplies the K indices
 // {4 c + q} of the 16 that the four lane groups hold, the same set on both
 // sides.
-//   - MFMA-bound from some tens of rows per expert on: wave w multiplies all
-//     rows, in steps of 16 (MF = 1..8 fragments), by 32 weight rows, so that
-//     the work follows the rows more closely than a 2 x 2 arrangement of the
-//     waves would (steps of 32).
+// MFMA-bound from some tens of rows per expert on: wave w multiplies all rows,
+// in steps of 16 (MF = 1..8 fragments), by 32 weight rows, so that the work
+// follows the rows more closely than a 2 x 2 arrangement of the waves would
+// (steps of 32).
 // Against 64 x 64 tiles on the vector ALUs, Qwen1.5-MoE shape with 500 tokens
 // and half the channels: 1388 -> 538 us; the 256-wide layer of the parity tests
 // with 64 tokens: 98 -> 36 us.

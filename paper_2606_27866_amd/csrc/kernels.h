@@ -51,7 +51,8 @@ struct Gemm1Params {
     int bm;
     // launch_gemm1_big_train only: the routed rows' activations h transposed --
     // element [c][prow0 + r] for row r of a segment -- with zeros in the rows
-    // [rows, packed_width(rows)) of each segment.  Row stride ldt.
+    // [rows, packed_width(rows)) of each segment; rows from there to the next
+    // segment are neither written nor read.  Row stride ldt.
     T* ht;
     int ldt;
 };

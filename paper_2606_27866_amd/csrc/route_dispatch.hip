@@ -31,7 +31,7 @@ __device__ __forceinline__ uint32_t route_key(float v) {
     return __builtin_isnan(v) ? 0u : k;
 }
 
-// Per-wave LDS scratch of route_token: the token's keys and the k slots.
+// Per-wave LDS scratch of route_tokens: one token's keys and its k slots.
 struct RouteScratch {
     uint32_t key[kMaxExperts];
     float slot_v[kMaxTopK];
