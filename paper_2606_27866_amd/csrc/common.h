@@ -126,12 +126,6 @@ __device__ __forceinline__ float wave_total_f(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 __device__ __forceinline__ float wave_sum_f(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -174,16 +168,6 @@ __device__ __forceinline__ int find_segment(const int32_t* tstart, int nseg, int
 __host__ __device__ __forceinline__ size_t frag_blocked(size_t r, int c, int C) {
     return (((r >> 5) * (size_t)(C >> 3) + (size_t)(c >> 3)) << 8) + (size_t)((((c >> 2) & 1) << 5) + (r & 31)) * 4 +
            (c & 3);
-}
-
-// Zero the bf16 elements at positions >= nvalid of an 8-element vector.
-__device__ __forceinline__ u32x4 mask_tail_bf16(u32x4 v, int nvalid) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (2 * i >= nvalid) v[i] = 0u;
-        else if (2 * i + 1 >= nvalid) v[i] &= 0xffffu;
-    }
-    return v;
 }
 
 }  // namespace flexmoe
