@@ -956,24 +956,24 @@ SalLayout sal_layout(const flexmoe_layer_desc& D, int T) { return sal_carve(D, T
 // transposed copies' rows; segments that start on 64-row boundaries put each
 // in one cache line instead of two (wgrad, Qwen1.5-MoE shape with 4096 and
 // 16384 tokens 600 -> 517 and 1690 -> 1328 us, Mixtral shape with 2048 2570 ->
-// 2074).  With few rows per expert, n = T top_k / E, writing the padding costs
-// more than it saves, and it saves more the more channel tiles read a row:
-// 64-row boundaries from n = kSalPadRows and n ceil(I / kSalTile) =
-// kSalPadReads on.  A batch with 8-row against 64-row boundaries: Qwen1.5-MoE
-// shape (6 channel tiles) at n = 8 / 17 / 34 / 51 / 68 644 / 660, 705 / 718,
-// 767 / 773, 809 / 807, 866 / 857 us; Mixtral shape (56) at n = 10 / 20 / 64
-// 1642 / 1650, 1673 / 1657, 2052 / 1948; 16 experts of 4096 channels (16) at
-// n = 8 / 25 468 / 478, 535 / 528.
+// 2074).  With few rows per expert, n = T top_k / E, most of what is written is
+// padding, and it saves the more the more channel tiles read a row: 64-row
+// boundaries from n = kSalPadRows on, and from kSalPadFewRows on where n
+// ceil(I / kSalTile) reaches kSalPadReads.  A batch with 8-row against 64-row
+// boundaries: Qwen1.5-MoE shape (6 channel tiles) at n = 8 / 17 / 34 / 51 / 68
+// 644 / 660, 705 / 718, 767 / 773, 809 / 807, 866 / 857 us; Mixtral shape (56) at
+// n = 10 / 20 / 64 1642 / 1650, 1673 / 1657, 2052 / 1948; 16 experts of 4096
+// channels (16) at n = 8 / 25 468 / 478, 535 / 528; with 1 or 2 tiles at n = 80
+// to 190 the two are within 1.5 %.
 // The wider copies fit the reported size when the caller brings the
 // transposed down weights, whose room they then take, on all but the smallest
 // layers; otherwise segments keep their 8-row boundaries.
-constexpr int kSalPadRows = 20, kSalPadReads = 256;
+constexpr int kSalPadRows = 48, kSalPadFewRows = 20, kSalPadReads = 320;
 SalLayout sal_layout_for(const flexmoe_layer_desc& D, int T, bool have_wdt) {
     const SalLayout S = sal_layout(D, T);
-    const long long A = (long long)T * D.top_k;
-    if (!have_wdt || A < (long long)kSalPadRows * D.E || A * S.nI < (long long)kSalPadReads * D.E ||
-        (long long)std::max(D.d, D.I) * sal_ldt(D, T, 64) >= (1LL << 30))
-        return S;
+    const long long A = (long long)T * D.top_k, E = D.E;
+    const bool rows = A >= kSalPadRows * E || (A >= kSalPadFewRows * E && A * S.nI >= kSalPadReads * E);
+    if (!have_wdt || !rows || (long long)std::max(D.d, D.I) * sal_ldt(D, T, 64) >= (1LL << 30)) return S;
     const SalLayout W = sal_carve(D, T, 64, false);
     return W.total <= S.total ? W : S;
 }

@@ -1,7 +1,7 @@
 """The saliency's transposed copies start every segment on a 64-row boundary
 when the caller brings the transposed down weights, the wider copies fit the
-reported workspace and the experts have rows enough (512 channels: 128 on
-average), else on an 8-row boundary: both give the oracle's scores, in a
+reported workspace and the experts have rows enough (48 on average, with many
+channels 20), else on an 8-row boundary: both give the oracle's scores, in a
 workspace of exactly the reported size that is followed by guard bytes.  Which
 one a call took is read from the workspace, where the transposed x is found by
 its first row."""
@@ -60,11 +60,11 @@ def transposed_row(x, lg, pad):
     (512, 512, MORE_ROWS, True, 64),                  # the wider copies take the room of the down weights
     (512, 512, MORE_ROWS, False, 8),                  # that room is taken
     (64, 72, MORE_ROWS, True, 8),                     # they do not fit
-    (512, 512, [130, 127, 128, 127], True, 64),       # 128 rows on average
-    (512, 512, [130, 127, 127, 127], True, 8),        # just below
-    (256, 3328, [17, 20, 23], True, 64),               # 20 rows on average, 13 channel tiles
-    (256, 3328, [17, 20, 22], True, 8),                # just below
-    (512, 512, ROWS, True, 8)])
+    (512, 512, [48, 47, 49, 48], True, 64),           # 48 rows on average
+    (512, 512, [48, 47, 48, 48], True, 8),            # just below
+    (176, 4096, [17, 20, 23], True, 64),              # 20 rows on average, 16 channel tiles
+    (176, 4096, [17, 20, 22], True, 8),               # just below
+    (176, 3840, [17, 20, 23], True, 8)])              # 15 channel tiles
 def test_segment_alignment_taken(d, I, rows, own_transpose, pad):
     import torch
     say("saliency alignment d", d, "I", I, "rows", rows, "own transpose", own_transpose)
