@@ -555,6 +555,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // 252 -> 246).
     const bool mid = bf16 && !decode && !train && sh_few &&
                      mid_tiles(T, D.top_k, D.E, D.I, D.d, has_shared, kComputeUnits);
+    const int nt_all = mid && use_side && mid_nt_all(D.E, D.I, D.d, D.I_shared);
     const int ks2 = train ? 0 : shared_ks2(D, T);
     const int parts = train ? (has_shared ? 1 : 0) : shared_parts(D, T);
     if (train == 2) {
@@ -626,6 +627,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                 p1.Gs = tr->Gs;
                 p1.Us = tr->Us;
             }
+            p1.nt_all = nt_all;
             {
                 KernelTimer kt(k1, st);
                 e = wide         ? launch_gemm1_decode_wide(p1, (int)n1, st)
@@ -642,6 +644,7 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
                                    seg_hi, (int)g2s, clipped};
             p2.order = ord2;
             p2.kept_only = train == 2;
+            p2.nt_all = nt_all;
             {
                 KernelTimer kt(k2, st);
                 e = wide     ? launch_gemm2_decode_wide(p2, (int)n2, st)

@@ -72,14 +72,17 @@ __device__ __forceinline__ void mid_tile(const Gemm1Params<bf16_t>& p1, const Ge
 
     // ---- operands: K range, buffer descriptors, row strides
     int K, lda, ldw;
+    uintptr_t wbits;  // the weight rows' first addresses and stride: their low bits
     __amdgpu_buffer_rsrc_t ra, rb;
     if constexpr (kGateUp) {
         K = lda = ldw = d;
         const RoutedWeights rw = shared ? RoutedWeights{0, p1.Is, 0} : routed_weights(p1, sm);
         // waves 0 and 1 request the gate rows, waves 2 and 3 the up rows
-        const bf16_t* W = (wave < MWAVES / 2 ? (shared ? p1.sg : p1.wg) : (shared ? p1.su : p1.wu)) + rw.base;
+        const bf16_t* Wg = (shared ? p1.sg : p1.wg) + rw.base;
+        const bf16_t* Wu = (shared ? p1.su : p1.wu) + rw.base;
+        wbits = (uintptr_t)Wg | (uintptr_t)Wu;
         ra = make_rsrc(p1.x, (size_t)p1.tokens * d);
-        rb = make_rsrc(W, (size_t)rw.rows * d);
+        rb = make_rsrc(wave < MWAVES / 2 ? Wg : Wu, (size_t)rw.rows * d);
     } else {
         const bool chunked = shared && p2.ks2 > 0;
         const int kbeg = chunked ? split * p2.ks2 : 0;
@@ -89,6 +92,7 @@ __device__ __forceinline__ void mid_tile(const Gemm1Params<bf16_t>& p1, const Ge
         ldw = rw.ldd;
         const bf16_t* Hb = (shared ? p2.Hs : p2.H + (size_t)sm.row0 * p2.I) + kbeg;
         const bf16_t* Wd = (shared ? p2.sd : p2.wd + rw.base) + kbeg;
+        wbits = (uintptr_t)Wd;
         ra = make_rsrc(Hb, (size_t)(shared ? p2.tokens : sm.rows) * lda - kbeg);
         rb = make_rsrc(Wd, (size_t)d * ldw - kbeg);
     }
@@ -117,7 +121,11 @@ __device__ __forceinline__ void mid_tile(const Gemm1Params<bf16_t>& p1, const Ge
     // hint (Qwen2-57B shape at 80 and 300 tokens 462 -> 420 and 563 -> 529 us,
     // Qwen1.5-MoE shape at 100 and 300 154 -> 136 and 172 -> 153; also on
     // weights that a second row tile reads again, Mixtral shape at 400 tokens,
-    // 446 -> 487 against 437 without).
+    // 446 -> 487 against 437 without).  Not on rows that start inside a 128-byte
+    // line: a K tile then shares its lines with the next, and the hint has them
+    // fetched twice (hidden size 1072, 35 experts of 1096 channels at 268 tokens
+    // 99 us with it, 71 without; 568, 58 of 1952 at 492 86.5 / 67.3) -- except
+    // beside a shared expert that ends later (mid_nt_all).
     auto run = [&](auto mf_tag, auto once_tag) {
         constexpr int MF = decltype(mf_tag)::value;
         constexpr bool kOnce = decltype(once_tag)::value;
@@ -248,7 +256,8 @@ __device__ __forceinline__ void mid_tile(const Gemm1Params<bf16_t>& p1, const Ge
         else if (tile_rows > 32) run(std::integral_constant<int, 2>{}, once);
         else run(std::integral_constant<int, 1>{}, once);
     };
-    if (mt == 1) by_rows(std::true_type{});
+    if (mt == 1 && ((kGateUp ? p1.nt_all : p2.nt_all) || ((wbits | (uintptr_t)ldw * 2) & 127) == 0))
+        by_rows(std::true_type{});
     else by_rows(std::false_type{});
 }
 

@@ -55,6 +55,7 @@ struct Gemm1Params {
     // segment are neither written nor read.  Row stride ldt.
     T* ht;
     int ldt;
+    int nt_all;  // 128 x 128 tiles: see mid_nt_all
 };
 
 // Down GEMM: O[row][n] = sum_{c < k_s} H[row][c] * W_down[n][c].  O holds one
@@ -86,6 +87,7 @@ struct Gemm2Params {
     // training forward (prefill tiles): reduce over the kept channels kk, not
     // over the GEMM width kg, which is I there
     int kept_only = 0;
+    int nt_all = 0;             // 128 x 128 tiles: see mid_nt_all
 };
 
 // Where routed expert e's weights live.  Ranked layout (online clipping):
@@ -204,6 +206,25 @@ inline bool mid_tiles(int T, int top_k, int E, int I, int d, bool has_shared, in
     if (A <= (long long)kMidRowsFull * E || has_shared) return true;
     const long long waves1 = (n1 + cu - 1) / cu, waves2 = (n2 + cu - 1) / cu, k = waves1 * d + waves2 * I;
     return 8 * (n1 * d + n2 * I) < 7 * k * cu || k < kMidFullK * (waves1 + waves2);
+}
+
+// Whether the 128 x 128 tiles read weights that one row tile uses with the
+// non-temporal hint even if their rows start inside 128-byte lines.  Such rows
+// are read faster without it (gemm_mid.hip), but plain reads of all routed
+// weights crowd out the operands of a shared expert on the side stream, whose
+// few large tiles then set the end.  So beside a side stream: while the routed
+// weights (6 E I d bytes at 5 TB/s) take less time than the shared expert's two
+// reductions, one tile after the other (1.5 us per K tile of 64, half as much
+// again beside the routed reads; the down one split from 1024 channels on).
+// With the hint / without: hidden size 3656, 51 experts of 328 and of 648
+// channels, shared 1320, 248 tokens 153 / 182 and 193 / 219 us; 3888, 37 of 416,
+// 6096, 444 tokens 129 / 151; past the line 3664, 30 of 2024, 1040, 127 tokens
+// 344 / 308; 1144, 61 of 968, 488, 144 tokens 117 / 99; 1200, 94 of 832, 552, 807
+// tokens 99 / 86.
+inline bool mid_nt_all(int E, int I, int d, int I_shared) {
+    const double routed_us = 6.0 * E * I * d / 5e6;
+    const double shared_us = 1.5 * 1.5 * (d + (I_shared < 1024 ? I_shared : 1024)) / 64;
+    return routed_us < shared_us;
 }
 
 __global__ void route_kernel(const float* logits, int T, int E, int k, int norm_topk, int32_t* idx,
