@@ -552,8 +552,8 @@ int forward_impl(const flexmoe_layer_desc* desc, int32_t T, const void* x, const
     // they are few (no-allocation forward, 60 % of the channels, large tiles
     // -> small: Qwen2-57B shape at 80 and 230 tokens 489 -> 444 and 536 -> 529
     // us, Qwen1.5-MoE shape at 100, 300 and 1000 155 -> 134, 171 -> 163 and
-    // 252 -> 246).
-    const bool mid = bf16 && !decode && !train && sh_few &&
+    // 252 -> 246; mid_one_launch has the other side).
+    const bool mid = bf16 && !decode && !train && sh_few && (use_side || mid_one_launch(T, D.d, D.I_shared)) &&
                      mid_tiles(T, D.top_k, D.E, D.I, D.d, has_shared, kComputeUnits);
     const int nt_all = mid && use_side && mid_nt_all(D.E, D.I, D.d, D.I_shared);
     const int ks2 = train ? 0 : shared_ks2(D, T);

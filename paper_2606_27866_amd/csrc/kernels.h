@@ -208,6 +208,21 @@ inline bool mid_tiles(int T, int top_k, int E, int I, int d, bool has_shared, in
     return 8 * (n1 * d + n2 * I) < 7 * k * cu || k < kMidFullK * (waves1 + waves2);
 }
 
+// Whether the shared expert's tiles may be 128 x 128 ones, which they are where
+// one launch covers it and routed experts that take them (no side stream).  Its
+// work bounds such a launch once it is large, and where its weight rows start
+// inside cache lines (128 bytes), every row piece a tile reads spans one line
+// more: small tiles read more of them for their flops.  No-allocation forward,
+// the weights of three and more layers in turn, small against large tiles: 49
+// shapes without whole lines and with 50 GFLOP or more, 6 % slower on average
+// (hidden size 1840, 29 experts of 328 channels, shared 8560, 572 tokens, 54
+// GFLOP: 136 / 106 us; 1528, 53 of 1128, 6104, 1299, 73: 188 / 169); at 40 to 50
+// GFLOP 2 % faster, below 30 19 %; with whole lines 2 % faster from 50 on.
+constexpr double kMidSharedFlops = 50e9;
+inline bool mid_one_launch(int T, int d, int I_shared) {
+    return ((d | I_shared) & 63) == 0 || 6.0 * T * d * I_shared < kMidSharedFlops;
+}
+
 // Whether the 128 x 128 tiles read weights that one row tile uses with the
 // non-temporal hint even if their rows start inside 128-byte lines.  Such rows
 // are read faster without it (gemm_mid.hip), but plain reads of all routed

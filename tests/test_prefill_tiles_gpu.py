@@ -1,6 +1,7 @@
 """Edges of the prefill tiles: segments of every row count around the 64-row
 steps of the MFMA work, reductions of one, two, three and four K tiles with
-and without a remainder, and channel counts around the tile's 128 channels."""
+and without a remainder, channel counts around the tile's 128 channels, and
+both sides of the lines between the tile shapes."""
 import numpy as np
 import pytest
 
@@ -127,11 +128,50 @@ def test_tile_rule_edges(T):
     layer.set_weights(*w)
     layer.set_budget(keep)
     y = layer.forward(x, lg).float()
-    p = torch.softmax(lg, 1)
-    ref = torch.zeros((T, d), device="cuda")
-    for e in range(E):
+    check_y(y.cpu().numpy(), top1_ref(x, lg, w, keep).cpu().numpy(), BF16_TOL)
+
+
+def top1_ref(x, lg, w, keep):
+    """The routed part of a top-1 layer in fp32 on the device."""
+    import torch
+    p, silu = torch.softmax(lg, 1), torch.nn.functional.silu
+    ref = torch.zeros(x.shape, device="cuda")
+    for e in range(lg.shape[1]):
         n, t = int(keep[e]), torch.nonzero(lg.argmax(1) == e).squeeze(1)
         xe = x[t].float()
-        h = torch.nn.functional.silu(xe @ w[0][e, :n].float().T) * (xe @ w[1][e, :n].float().T)
+        h = silu(xe @ w[0][e, :n].float().T) * (xe @ w[1][e, :n].float().T)
         ref[t] = p[t, e].unsqueeze(1) * (h @ w[2][e, :, :n].float().T)
-    check_y(y.cpu().numpy(), ref.cpu().numpy(), BF16_TOL)
+    return ref
+
+
+# 6 T d I_shared flops: 993 and 994 tokens are the sides of 50e9 at hidden size
+# 1000 and 8392 channels, whose weight rows end inside a cache line
+ONE_LAUNCH = [(993, 1000, 8392, True), (994, 1000, 8392, False), (994, 1024, 8448, True)]
+
+
+@pytest.mark.parametrize("T,d,I_s,small", ONE_LAUNCH)
+def test_shared_rule_edges(T, d, I_s, small):
+    """The forward whose one launch covers the shared expert too: the routed
+    experts (62 rows each) take its tiles."""
+    import torch
+    E, I = 16, 136
+    say("shared rule T", T, "d", d, "I_s", I_s)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T + d)
+
+    def rnd(*shape, std=0.02):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=gen)
+
+    w = [rnd(E, I, d), rnd(E, I, d), rnd(E, d, I)]
+    s = [rnd(I_s, d), rnd(I_s, d), rnd(d, I_s)]
+    x, lg = rnd(T, d, std=1.0), torch.randn((T, E), device="cuda", generator=gen)
+    keep = np.array([I, 0, 1, 127, 128, 129, 100, I - 1] * 2, np.int32)
+    layer = fm.Layer(d, E, I, 1, I_s, synth.BF16, 0, max_tokens=T)
+    layer.set_weights(*w, *s)
+    layer.set_budget(keep)
+    y = torch.empty_like(x)
+    fm.flexmoe_layer_forward_noalloc(layer.desc, T, x, lg, *w, layer.keep, *s, y)
+    xf = x.float()
+    h = torch.nn.functional.silu(xf @ s[0].float().T) * (xf @ s[1].float().T)
+    ref = top1_ref(x, lg, w, keep) + h @ s[2].float().T
+    check_y(y.float().cpu().numpy(), ref.cpu().numpy(), BF16_TOL)
