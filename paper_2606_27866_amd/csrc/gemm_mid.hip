@@ -123,9 +123,10 @@ __device__ __forceinline__ void mid_tile(const Gemm1Params<bf16_t>& p1, const Ge
     // weights that a second row tile reads again, Mixtral shape at 400 tokens,
     // 446 -> 487 against 437 without).  Not on rows that start inside a 128-byte
     // line: a K tile then shares its lines with the next, and the hint has them
-    // fetched twice (hidden size 1072, 35 experts of 1096 channels at 268 tokens
-    // 99 us with it, 71 without; 568, 58 of 1952 at 492 86.5 / 67.3) -- except
-    // beside a shared expert that ends later (mid_nt_all).
+    // fetched twice (top-4, hidden size 1072, 35 experts of 1096 channels at 268
+    // tokens 72.4 us with it, 70.9 without; 568, 58 of 1952 at 492 97.7 / 93.7;
+    // where the weights stay in the last-level cache 99 / 71 and 86.5 / 67.3) --
+    // except beside a shared expert that ends later (mid_nt_all).
     auto run = [&](auto mf_tag, auto once_tag) {
         constexpr int MF = decltype(mf_tag)::value;
         constexpr bool kOnce = decltype(once_tag)::value;

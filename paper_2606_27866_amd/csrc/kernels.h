@@ -231,11 +231,12 @@ inline bool mid_one_launch(int T, int d, int I_shared) {
 // weights (6 E I d bytes at 5 TB/s) take less time than the shared expert's two
 // reductions, one tile after the other (1.5 us per K tile of 64, half as much
 // again beside the routed reads; the down one split from 1024 channels on).
-// With the hint / without: hidden size 3656, 51 experts of 328 and of 648
-// channels, shared 1320, 248 tokens 153 / 182 and 193 / 219 us; 3888, 37 of 416,
-// 6096, 444 tokens 129 / 151; past the line 3664, 30 of 2024, 1040, 127 tokens
-// 344 / 308; 1144, 61 of 968, 488, 144 tokens 117 / 99; 1200, 94 of 832, 552, 807
-// tokens 99 / 86.
+// With the hint / without, top-4, 60 % of the channels, the weights of several
+// layers in turn: hidden size 3656, 51 experts of 328 and of 648 channels, shared
+// 1320, 248 tokens 139 / 181 and 176 / 207 us; past the line 3664, 30 of 2024,
+// 1040, 127 tokens 249 / 226; 1144, 61 of 968, 488, 144 tokens 96 / 88; 1200, 94
+// of 832, 552, 807 tokens 131 / 126.  (One layer repeated, its weights in the
+// last-level cache, loses more by the hint: the last two 117 / 99 and 99 / 86.)
 inline bool mid_nt_all(int E, int I, int d, int I_shared) {
     const double routed_us = 6.0 * E * I * d / 5e6;
     const double shared_us = 1.5 * 1.5 * (d + (I_shared < 1024 ? I_shared : 1024)) / 64;
